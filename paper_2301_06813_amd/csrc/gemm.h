@@ -115,7 +115,10 @@ hipError_t launch_split_reduce_pair(const Gemm &gd, int sd, const float *wsd, co
 bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw);
 hipError_t launch_bf16_bwd_group(const Gemm &gd, const Plan &pd, const Gemm &gw,
                                  const Plan &pw, float *ws, hipStream_t s);
-hipError_t launch_f32(const Gemm &g, hipStream_t s);
+// fp32 products: as plan_bf16 and launch_bf16 (kblk_per_split in 32-wide blocks,
+// dma false: the plain FMA kernel).
+Plan plan_f32(const Gemm &g);
+hipError_t launch_f32(const Gemm &g, const Plan &p, float *ws, hipStream_t s);
 
 // The library's static scratch on the current device (its address there,
 // looked up once per device) and its size in floats (WS_FLOATS_PREFERRED).

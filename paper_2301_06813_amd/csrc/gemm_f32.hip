@@ -1,18 +1,45 @@
 // gemm_f32.hip -- fp32-input path of the local matmul and the bf16 dispatch
 // by orientation.
 //
-// The fp32 path serves fp32 workloads (small layers trained in single
-// precision). It is a plain LDS-tiled fp32 FMA kernel: 64 x 64 output tile,
-// reduction step 16, 256 threads each owning a 4 x 4 strided sub-block, so
-// that global loads and stores are coalesced for every operand orientation.
-// Products and sums are single fp32 FMAs; the reduction order is
-// increasing k.
+// The fp32 path serves fp32 training (the paper's P100 runs are fp32). Two
+// kernels: the matrix-core kernel below for every product whose tiles fit
+// 31-bit buffer offsets, and a plain FMA kernel for leading dimensions beyond
+// that (2^21 elements).
+//
+// Matrix-core kernel (gemm_f32_mfma_kernel), bound by the fp32 MFMA rate:
+//   * v_mfma_f32_32x32x2_f32: fp32 products and sums, 256 flop/clk/CU -- the
+//     same fp32 arithmetic as FMAs, in another order of k.
+//   * Four waves (2 x 2), 128 x 128 or 64 x 64 output tile, 32-wide reduction
+//     steps; two stages of both operand tiles in LDS, loaded by buffer loads
+//     that write LDS directly. A 128 x 128 step is 4096 cycles of MFMA per
+//     32 KB of operands, so one stage ahead and a second workgroup per CU
+//     (four or five of the 64 x 64 ones) cover the memory latency, barriers
+//     and epilogues. More stages (three to eight) with fewer workgroups per
+//     CU, or two reduction groups of waves, were no faster; 128 x 64 tiles
+//     lay between the two.
+//   * Measured, against the FMA kernel below: 1024 x 4096 x 1024 forward
+//     240 -> 75 us, 256 x 4096 x 3136 forward 660 -> 63 us, 4096^3 134
+//     TFLOP/s (the library product reaches 141); the largest error against
+//     64 bits over fp32 layers of those sizes 1.1e-6 -> 7.1e-7.
+//   * V = 4: 16 bytes per lane, where both operands' base, ld and contiguous
+//     extent are multiples of 4 floats. V = 1: 4 bytes per lane with per-element
+//     bounds, for any other operand: four times the load instructions, which
+//     still fit under the MFMA time of a step.
+//   * k-major tiles: 128-byte rows (32 reduction values) of eight 16-byte
+//     chunks, chunk c of row r at c ^ ((r / 2) % 8), so a 16-row
+//     ds_read_b128 phase covers all 64 banks; lane l takes chunk 2 j + l / 32,
+//     i.e. MFMA e of group j multiplies k = 8 j + e (lower half-wave) and
+//     8 j + 4 + e (upper half).
+//   * m/n-major tiles: rows of BM (BN) values per reduction index, read with
+//     ds_read_b32 at the same k; chunks of rows with odd k / 4 are shifted by
+//     8 so that the two half-waves use different banks.
+//   * Split reduction as in the bf16 kernels (split_reduce.hip adds the fp32
+//     partials in split order).
 #include "gemm.h"
+#include "gemm_bf16_dma.h"
 #include "profile.h"
 
 namespace sbpk {
-
-constexpr int F_BM = 64, F_BN = 64, F_BK = 16;
 
 struct F32Args {
     const float *A;
@@ -20,9 +47,166 @@ struct F32Args {
     float *C;
     int64_t lda, ldb, ldc;
     int32_t m, n, k;
-    int32_t tiles_n;
-    int32_t accumulate;   // add the product to C's contents
+    int32_t tiles_m, tiles_n;
+    int32_t splits, kchunk;   // reduction elements per split (a multiple of 32)
+    float *ws;                // split partials, row stride partial_ld(n)
+    int32_t accumulate;       // add the product to C's contents
 };
+
+// One 4-byte-per-lane buffer load that writes LDS directly (see dma16).
+__device__ __forceinline__ void dma4(i32x4 r, char *lds, int voff) {
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uintptr_t)(SBP_LDS void *)lds);
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(m0), "v"(voff), "s"(r)
+                 : "memory", "m0");
+}
+
+constexpr int FK = 32;   // reduction elements per step
+
+// Operand tile of BMN output indices x FK reduction indices (layouts above).
+template <int BMN, bool KMAJ, int V>
+struct F32Tile {
+    static constexpr int LOADS = BMN * FK / (64 * V * 4);   // per wave (4 waves)
+
+    __device__ __forceinline__ static int swz(int row) {
+        return KMAJ ? (row >> 1) & 7 : ((row >> 2) & 1) << 3;
+    }
+
+    __device__ __forceinline__ static void issue(const float *base, int64_t ld, int mn0,
+                                                 int mn_lim, int k0, int k_lim, char *lds,
+                                                 int wave, int lane) {
+        constexpr int ROW = KMAJ ? FK : BMN;   // floats per LDS row
+        const i32x4 r = make_rsrc(KMAJ ? base + (int64_t)mn0 * ld + k0
+                                       : base + (int64_t)k0 * ld + mn0);
+        // rows left along the row index, elements left along the contiguous one
+        const int rows = KMAJ ? mn_lim - mn0 : k_lim - k0;
+        const int cols = KMAJ ? k_lim - k0 : mn_lim - mn0;
+        const int ldi = (int)ld;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int seg = (i * 4 + wave) * 64 * V;
+            const int pos = seg + lane * V;
+            const int row = pos / ROW, in = pos % ROW;
+            const int col = (((in >> 2) ^ swz(row)) << 2) + (in & 3);
+            const bool ok = row < rows && col + V <= cols;
+            const int voff = ok ? (row * ldi + col) * 4 : OOB;
+            if constexpr (V == 4) dma16(r, lds + seg * 4, voff);
+            else dma4(r, lds + seg * 4, voff);
+        }
+    }
+
+    // Values k = 8 j + 4 (lane / 32) + 0..3 of output index c0 + lane % 32.
+    __device__ __forceinline__ static f32x4 frag(const char *lds, int c0, int j, int lane) {
+        const int mn = c0 + (lane & 31);
+        if constexpr (KMAJ) {
+            const int c = 2 * j + (lane >> 5);
+            return *reinterpret_cast<const f32x4 *>(lds + mn * FK * 4 + ((c ^ swz(mn)) << 4));
+        } else {
+            const int k = 8 * j + 4 * (lane >> 5);   // rows k .. k+3 share one swizzle
+            const float *p = reinterpret_cast<const float *>(lds) + k * BMN +
+                             ((((mn >> 2) ^ swz(k)) << 2) | (mn & 3));
+            f32x4 v = {p[0], p[BMN], p[2 * BMN], p[3 * BMN]};
+            return v;
+        }
+    }
+};
+
+template <int BM, int BN, bool A_KMAJ, bool B_KMAJ, int V>
+__global__ __launch_bounds__(256, BM == 64 ? 4 : 2) void gemm_f32_mfma_kernel(F32Args g) {
+    using TA = F32Tile<BM, A_KMAJ, V>;
+    using TB = F32Tile<BN, B_KMAJ, V>;
+    constexpr int A_BYTES = BM * FK * 4, STAGE = (BM + BN) * FK * 4;
+    constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 32, NI = WN / 32;
+    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+
+    const int tiles = g.tiles_m * g.tiles_n;
+    const int L = remap_xcd(blockIdx.x, tiles * g.splits);
+    const int split = L / tiles;
+    const int t = L % tiles;
+    constexpr int GROUP = SBP_TILE_GROUP;
+    const int grp = t / (GROUP * g.tiles_n);
+    const int first_m = grp * GROUP;
+    const int gsize = min(g.tiles_m - first_m, GROUP);
+    const int tg = t - grp * GROUP * g.tiles_n;
+    const int m0 = (first_m + tg % gsize) * BM, n0 = (tg / gsize) * BN;
+    const int k_begin = split * g.kchunk;
+    const int k_lim = min(g.k, k_begin + g.kchunk);
+    const int nkb = max(0, (k_lim - k_begin + FK - 1) / FK);
+
+    auto issue = [&](int kb, int stage) {
+        char *base = smem + stage * STAGE;
+        const int k0 = k_begin + kb * FK;
+        TA::issue(g.A, g.lda, m0, g.m, k0, k_lim, base, wave, lane);
+        TB::issue(g.B, g.ldb, n0, g.n, k0, k_lim, base + A_BYTES, wave, lane);
+    };
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    if (nkb > 0) issue(0, 0);
+    for (int it = 0; it < nkb; ++it) {
+        // this thread's loads of step `it` are done, then everyone's; the
+        // stage read last step is free to refill
+        wait_vm<0>();
+        __syncthreads();
+        if (it + 1 < nkb) issue(it + 1, (it + 1) & 1);
+        const char *cur = smem + (it & 1) * STAGE;
+#pragma unroll
+        for (int j = 0; j < FK / 8; ++j) {
+            f32x4 a[MI], b[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) a[i] = TA::frag(cur, wm * WM + i * 32, j, lane);
+#pragma unroll
+            for (int i = 0; i < NI; ++i) b[i] = TB::frag(cur + A_BYTES, wn * WN + i * 32, j, lane);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int jj = 0; jj < NI; ++jj)
+                        acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[jj][e],
+                                                                          acc[i][jj], 0, 0, 0);
+        }
+    }
+
+    // lane holds column lane % 32 of a 32 x 32 block, register r row
+    // 8 (r / 4) + 4 (lane / 32) + r % 4
+    const bool partial = g.splits > 1;
+    const int64_t ldo = partial ? sbpi::partial_ld(g.n) : g.ldc;
+    float *const out = partial ? g.ws + (size_t)split * (size_t)g.m * (size_t)ldo : g.C;
+    const __amdgpu_buffer_rsrc_t pr = part_rsrc(out);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int col = n0 + wn * WN + j * 32 + (lane & 31);
+            const int rbase = m0 + wm * WM + i * 32 + 4 * (lane >> 5);
+            if (col >= g.n) continue;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = rbase + 8 * (r >> 2) + (r & 3);
+                if (row >= g.m) continue;
+                float *c = out + (int64_t)row * ldo + col;
+                if (partial) st_part(pr, (int64_t)row * ldo + col, acc[i][j][r]);
+                else if (g.accumulate) *c = *c + acc[i][j][r];
+                else st_nt(c, acc[i][j][r]);
+            }
+        }
+}
+
+// Plain LDS-tiled FMA kernel for leading dimensions beyond 2^21: 64 x 64
+// output tile, reduction step 16, 256 threads each owning a 4 x 4 strided
+// sub-block.
+constexpr int F_BM = 64, F_BN = 64, F_BK = 16;
 
 template <bool A_KMAJ, bool B_KMAJ>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args g) {
@@ -107,7 +291,10 @@ hipError_t launch_bf16(const Gemm &g, const Plan &p, float *ws, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_f32(const Gemm &g, hipStream_t s) {
+template <bool AK, bool BK_>
+static hipError_t launch_f32_orient(const Gemm &g, const Plan &p, float *ws, hipStream_t s) {
+    const char *tf[2] = {"false", "true"};
+    char name[96];
     sbpk::F32Args a;
     a.A = static_cast<const float *>(g.A);
     a.B = static_cast<const float *>(g.B);
@@ -118,20 +305,44 @@ hipError_t launch_f32(const Gemm &g, hipStream_t s) {
     a.m = (int32_t)g.m;
     a.n = (int32_t)g.n;
     a.k = (int32_t)g.k;
+    a.tiles_m = (int32_t)((g.m + p.bm - 1) / p.bm);
+    a.tiles_n = (int32_t)((g.n + p.bn - 1) / p.bn);
+    a.splits = p.splits;
+    a.kchunk = p.kblk_per_split * p.bk;
+    a.ws = ws;
     a.accumulate = g.accumulate;
-    const int tiles_m = (int)((g.m + sbpk::F_BM - 1) / sbpk::F_BM);
-    a.tiles_n = (int)((g.n + sbpk::F_BN - 1) / sbpk::F_BN);
-    const int grid = tiles_m * a.tiles_n;
+    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n * a.splits));
+    if (!p.dma) {
+        snprintf(name, sizeof(name), "gemm_f32_kernel<%s, %s>", tf[AK], tf[BK_]);
+        return launch_kernel(sbpk::gemm_f32_kernel<AK, BK_>, name, grid, dim3(256), s, a);
+    }
+    // 16-byte loads need every row of both operands on 16-byte chunks
+    const bool v4 =
+        ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) == 0 &&
+        g.lda % 4 == 0 && g.ldb % 4 == 0 && (AK ? g.k : g.m) % 4 == 0 &&
+        (BK_ ? g.k : g.n) % 4 == 0;
+    hipError_t e = hipErrorInvalidValue;
+#define SBP_F32_TILE(BM_)                                                                    \
+    if (p.bm == BM_) {                                                                       \
+        snprintf(name, sizeof(name), "gemm_f32_mfma_kernel<%d, %d, %s, %s, %d>", BM_, BM_,   \
+                 tf[AK], tf[BK_], v4 ? 4 : 1);                                               \
+        e = v4 ? launch_kernel(sbpk::gemm_f32_mfma_kernel<BM_, BM_, AK, BK_, 4>, name, grid, \
+                               dim3(256), s, a)                                              \
+               : launch_kernel(sbpk::gemm_f32_mfma_kernel<BM_, BM_, AK, BK_, 1>, name, grid, \
+                               dim3(256), s, a);                                             \
+    }
+    SBP_F32_TILE(128)
+    SBP_F32_TILE(64)
+#undef SBP_F32_TILE
+    if (e != hipSuccess || p.splits == 1) return e;
+    return launch_split_reduce(g, p.splits, ws, s);
+}
+
+hipError_t launch_f32(const Gemm &g, const Plan &p, float *ws, hipStream_t s) {
     switch (g.orient) {
-        case OR_FWD:
-            return launch_kernel(sbpk::gemm_f32_kernel<true, false>,
-                                 "gemm_f32_kernel<true, false>", dim3(grid), dim3(256), s, a);
-        case OR_BWD_DATA:
-            return launch_kernel(sbpk::gemm_f32_kernel<true, true>,
-                                 "gemm_f32_kernel<true, true>", dim3(grid), dim3(256), s, a);
-        case OR_BWD_WEIGHT:
-            return launch_kernel(sbpk::gemm_f32_kernel<false, false>,
-                                 "gemm_f32_kernel<false, false>", dim3(grid), dim3(256), s, a);
+        case OR_FWD: return launch_f32_orient<true, false>(g, p, ws, s);
+        case OR_BWD_DATA: return launch_f32_orient<true, true>(g, p, ws, s);
+        case OR_BWD_WEIGHT: return launch_f32_orient<false, false>(g, p, ws, s);
     }
     return hipErrorInvalidValue;
 }

@@ -565,4 +565,45 @@ static Plan plan_uncached(const Gemm &g) {
     return best;
 }
 
+// fp32 products (gemm_f32.hip). Measured on MI355X, a 32-wide reduction step of
+// a 128 x 128 tile takes a compute unit 2.1 us however many workgroups share
+// it (fp32 MFMA bound); one of a 64 x 64 tile 0.55 us when two or more
+// workgroups share the unit and 0.76 us alone, where nothing hides its load
+// latency. So small outputs split their reduction until every unit has
+// several 64 x 64 workgroups (1024 x 1024 x 4096: 98 us unsplit, 79 us split
+// four ways), and outputs of a whole wave of 128 x 128 tiles take those
+// (4096^3: 1028 us against 1068 us; 1024 x 4096 x 1024: 75 us for both).
+Plan plan_f32(const Gemm &g) {
+    constexpr int64_t kMaxLd = int64_t(1) << 21;   // tile offsets stay below 2^31 bytes
+    const int kb = (int)((g.k + 31) / 32);
+    Plan best{64, 64, 1, std::max(1, kb), false};
+    best.bk = 32;
+    if (g.lda > kMaxLd || g.ldb > kMaxLd) return best;   // plain FMA kernel
+    best.dma = true;
+    double best_t = 1e30;
+    for (const int t : {64, 128}) {
+        const double nt = (double)((g.m + t - 1) / t) * (double)((g.n + t - 1) / t);
+        int last = 0;
+        for (int s = 1; s <= 32; ++s) {
+            int splits, per;
+            split_of(kb, s, &splits, &per);
+            if (splits == last) continue;
+            last = splits;
+            if (splits > 1 && (per < 4 || !fits_ws(g, splits))) continue;
+            // work items of the busiest unit; beyond four the units even out
+            const double q = nt * splits / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
+            const double step = t == 128 ? 2.1e-6 : q <= 1.0 ? 0.76e-6 : 0.55e-6;
+            double tm = busy * per * step + 6e-6;
+            if (splits > 1) tm += (splits * 2.0 + 1.0) * 4.0 * g.m * g.n / 8e12 + 2.5e-6;
+            if (tm < best_t * 0.999) {
+                best_t = tm;
+                best.bm = best.bn = t;
+                best.splits = splits;
+                best.kblk_per_split = per;
+            }
+        }
+    }
+    return best;
+}
+
 }  // namespace sbpi

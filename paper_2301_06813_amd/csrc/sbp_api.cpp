@@ -228,14 +228,11 @@ bool ws_disjoint(const Ws &w, const sbpi::Gemm &g) {
 int run(sbpi::Gemm g, const Ws &w, hipStream_t s) {
     if (g.m == 0 || g.n == 0) return SBP_OK;
     hipError_t e;
-    if (g.in_dtype == SBP_F32) {
-        e = sbpi::launch_f32(g, s);
-    } else {
-        g.ws_floats = w.floats;
-        const sbpi::Plan p = sbpi::plan_bf16(g);
-        if (sbpi::plan_ws_floats(g, p) > w.floats) return SBP_ERR_WORKSPACE;
-        e = sbpi::launch_bf16(g, p, w.ptr, s);
-    }
+    g.ws_floats = w.floats;
+    const bool f32 = g.in_dtype == SBP_F32;
+    const sbpi::Plan p = f32 ? sbpi::plan_f32(g) : sbpi::plan_bf16(g);
+    if (sbpi::plan_ws_floats(g, p) > w.floats) return SBP_ERR_WORKSPACE;
+    e = f32 ? sbpi::launch_f32(g, p, w.ptr, s) : sbpi::launch_bf16(g, p, w.ptr, s);
     if (e != hipSuccess) {
         g_last_hip = (int)e;
         return SBP_ERR_HIP;
@@ -771,23 +768,17 @@ int sbp_plan(int op, int64_t m, int64_t n, int64_t k, int32_t in_dtype, int32_t 
     if ((in_dtype != SBP_BF16 && in_dtype != SBP_F32) ||
         (out_dtype != SBP_BF16 && out_dtype != SBP_F32))
         return SBP_ERR_DTYPE;
-    if (in_dtype == SBP_F32) {
-        *tile_m = 64;
-        *tile_n = 64;
-        *splits = 1;
-        *kernel = 3;
-        return SBP_OK;
-    }
     // Plan for 16-byte aligned operands with tight leading dimensions.
     static const char aligned[16] __attribute__((aligned(16))) = {0};
     const int64_t lda = (op == 2) ? m : k, ldb = (op == 1) ? k : n;
     sbpi::Gemm g{op, in_dtype, out_dtype, aligned, lda, aligned, ldb, nullptr, 0, m, n, k};
     g.ws_floats = sbpi::WS_FLOATS_PREFERRED;
-    sbpi::Plan p = sbpi::plan_bf16(g);
+    const bool f32 = in_dtype == SBP_F32;
+    const sbpi::Plan p = f32 ? sbpi::plan_f32(g) : sbpi::plan_bf16(g);
     *tile_m = p.bm;
     *tile_n = p.bn;
     *splits = p.splits;
-    *kernel = sbpi::kernel_code(p);
+    *kernel = f32 ? 3 : sbpi::kernel_code(p);
     return SBP_OK;
 }
 

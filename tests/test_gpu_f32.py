@@ -1,0 +1,80 @@
+"""fp32-input products at the edges of their kernels: tiles and remainders,
+16-byte and element-wise loads, split reductions, leading dimensions beyond
+the matrix-core kernel's, special values.
+
+Integer inputs whose sums stay below 2^24 are exact in fp32 whatever the
+order of the sums, so whole outputs must equal the fp64 product.
+"""
+import pytest
+import torch
+
+from paper_2301_06813_amd import linear, sbp
+
+from helpers import say
+
+pytestmark = pytest.mark.gpu
+F32 = sbp.SBP_F32
+
+
+def _ints(rows, cols, pad, off, seed):
+    """Integers in [-4, 4] as a view at column `off` of NaN-filled storage."""
+    g = torch.Generator().manual_seed(seed)
+    big = torch.full((rows + 1, off + cols + pad), float("nan"), device="cuda")
+    v = big[:rows, off:off + cols]
+    v.copy_(torch.randint(-4, 5, (rows, cols), generator=g).float())
+    return v
+
+
+@pytest.mark.parametrize("pad,off", [(0, 0), (8, 4), (0, 1), (3, 0)],
+                         ids=["tight", "padded", "odd-offset", "odd-ld"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (64, 128, 64), (65, 97, 130), (4, 4100, 12),
+                                   (257, 1000, 129), (640, 31, 2048), (1536, 260, 1664)])
+def test_f32_exact_edges(shape, pad, off):
+    M, K, N = shape
+    X, W, dY = (_ints(a, b, pad, off, 40 + i) for i, (a, b) in
+                enumerate(((M, K), (K, N), (M, N))))
+    L = linear.layouts("BB", 1, 0)
+    Xd, Wd, dYd = (t.cpu().double() for t in (X, W, dY))
+    want = {"fwd": Xd @ Wd, "bwd_data": dYd @ Wd.t(), "bwd_weight": Xd.t() @ dYd}
+    for op, w in want.items():
+        for acc in (False, True):
+            say("f32", shape, pad, off, op, acc)
+            guard = torch.full((w.shape[0] + 2, w.shape[1] + 3), 5.0, device="cuda")
+            out = guard[1:-1, 1:-2]
+            linear.run_L(op, L, X, W, dY, out, accumulate=acc)
+            got = out.cpu().double()
+            assert torch.equal(got, w + 5.0 if acc else w)
+            out.fill_(5.0)
+            assert bool((guard == 5.0).all())
+
+
+def test_f32_plans_reach_both_tiles_and_splits():
+    plans = [sbp.sbp_plan(0, m, n, k, F32, F32) for m, n, k in
+             ((1536, 1664, 260), (2048, 2048, 256), (4096, 4096, 512), (4, 12, 4100))]
+    assert {p[0] for p in plans} == {64, 128}
+    assert min(p[2] for p in plans) == 1 and max(p[2] for p in plans) > 1
+    assert all(p[3] == sbp.KERNEL_F32 for p in plans)
+
+
+def test_f32_leading_dimension_beyond_buffer_offsets():
+    ld = (1 << 21) + 4
+    X = torch.randint(-4, 5, (3, ld), device="cuda").float()[:, :70]
+    W = torch.randint(-4, 5, (70, 40), device="cuda").float()
+    out, _ = linear.call("fwd", "BB", 1, 0, X, W, None)
+    assert torch.equal(out.cpu().double(), X.cpu().double() @ W.cpu().double())
+
+
+def test_f32_special_values_stay_in_their_row():
+    X = torch.ones(70, 66)
+    X[3, 5], X[9, 65], X[69, 0] = float("inf"), float("nan"), -float("inf")
+    X[20, :] = 1e-40   # subnormal inputs and products
+    W = torch.rand(66, 70) + 1
+    out = linear.call("fwd", "BB", 1, 0, X.cuda(), W.cuda(), None)[0].cpu()
+    assert torch.isposinf(out[3]).all() and torch.isneginf(out[69]).all()
+    assert torch.isnan(out[9]).all()
+    rest = [i for i in range(70) if i not in (3, 9, 69)]
+    want = (X.double() @ W.double())[rest]
+    # 66 fp32 roundings, each at most 2^-24 of a partial sum of positive terms,
+    # and at most half the smallest subnormal (2^-150) absolutely
+    err = (out[rest].double() - want).abs()
+    assert bool((err <= 66 * (2.0 ** -24 * want + 2.0 ** -149)).all())
