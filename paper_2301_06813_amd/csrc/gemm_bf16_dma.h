@@ -1,9 +1,11 @@
-// gemm_bf16_dma.h -- pipelined bf16 MFMA GEMM with direct global->LDS loads
-// (CDNA4 / gfx950). Same contract and operand orientations as
-// gemm_bf16_kernel.h; used when every operand is 16-byte aligned with a
-// leading dimension and a contiguous extent that are multiples of 8
-// elements, so each 16-byte chunk of an operand is either wholly inside or
-// wholly outside it.
+// gemm_bf16_dma.h -- bf16 MFMA GEMM kernels (CDNA4 / gfx950; contract and operand
+// orientations in gemm_bf16_kernel.h): a pipelined kernel with direct
+// global->LDS loads, used when every operand is 16-byte aligned with a leading
+// dimension and a contiguous extent that are multiples of 8 elements, so each
+// 16-byte chunk of an operand is either wholly inside or wholly outside it (and
+// its shifted form, see GemmArgsShift); and a generic kernel for any other
+// operand, with the same LDS layouts, fragment reads and epilogues but loads
+// that go through registers (RegTile).
 //
 // Design:
 //   * Workgroups of 4 waves (2 x 2) or 8 waves (2 x 4, two per SIMD, for
@@ -208,6 +210,106 @@ template <int BMN, int NW, int BK_, bool KMAJ>
 using DmaTileOf =
     typename std::conditional<KMAJ, KTileDma<BMN, NW, BK_>, MNTileDma<BMN, NW, BK_>>::type;
 
+// 16 bytes at any element alignment (one global load; the hardware splits it
+// where it crosses a line).
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+__device__ __forceinline__ u32x4 ld16_any(const uint16_t *p) {
+    return *reinterpret_cast<const u32x4_any *>(p);
+}
+
+// Elements [at, at + 8) of a row of `lim` elements at `row` (0 beyond it; at < lim,
+// at + 8 > lim): the row's last 8 elements, shifted down.
+__device__ __forceinline__ u32x4 ld16_tail(const uint16_t *row, int at, int lim) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (lim < 8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (at + e < lim) v[e >> 1] |= (uint32_t)row[at + e] << (16 * (e & 1));
+        return v;
+    }
+    const u32x4 x = ld16_any(row + lim - 8);
+    const int sh = 16 * (at + 8 - lim);   // 16 .. 112 bits
+    uint64_t lo = x[0] | ((uint64_t)x[1] << 32), hi = x[2] | ((uint64_t)x[3] << 32);
+    if (sh >= 64) {
+        lo = hi >> (sh - 64);
+        hi = 0;
+    } else {
+        lo = (lo >> sh) | (hi << (64 - sh));
+        hi >>= sh;
+    }
+    v[0] = (uint32_t)lo;
+    v[1] = (uint32_t)(lo >> 32);
+    v[2] = (uint32_t)hi;
+    v[3] = (uint32_t)(hi >> 32);
+    return v;
+}
+
+// Operand tile moved to LDS through registers, for operands that the
+// direct-to-LDS loads cannot read (rows at any element alignment). The LDS
+// layout is that of DmaTileOf, so both share the fragment reads. Indices past
+// an output bound read some other element of the operand (or 0): they feed
+// only outputs that are never stored. Reduction indices past k_lim are 0.
+template <int BMN, int NW, bool KMAJ>
+struct RegTile {
+    using T = DmaTileOf<BMN, NW, 64, KMAJ>;
+    static constexpr int NV = BMN * 8 / (64 * NW);   // 16-byte chunks per thread
+    static constexpr int CPR = KMAJ ? 8 : BMN / 8;   // chunks per row
+    typedef u32x4 Regs[NV];
+    const uint16_t *p[NV];   // this thread's chunks of the next whole step
+
+    // Whole steps, which read 64 reduction indices without a bounds check, are
+    // those before k_lim; where the tile hangs over the end of m/n-major rows,
+    // a row's last chunk may run up to 7 elements into the next row, so the
+    // operand's last row is left to load_edge (and rows shorter than 8 are).
+    __device__ __forceinline__ static int whole_steps(int mn0, int mn_lim, int k_begin, int k_lim,
+                                                      int k_end) {
+        if (KMAJ || mn0 + BMN <= mn_lim) return (k_lim - k_begin) >> 6;
+        return mn_lim < 8 ? 0 : max(0, min(k_lim, k_end - 1) - k_begin) >> 6;
+    }
+    __device__ __forceinline__ void init(const uint16_t *base, int64_t ld, int mn0, int mn_lim,
+                                         int k0, int tid) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int q = i * 64 * NW + tid;
+            p[i] = KMAJ ? base + (int64_t)min(mn0 + q / CPR, mn_lim - 1) * ld + k0 + (q % CPR) * 8
+                        : base + (int64_t)(k0 + q / CPR) * ld +
+                              min(mn0 + (q % CPR) * 8, (mn_lim - 1) & ~7);
+        }
+    }
+    __device__ __forceinline__ void load(Regs &v, int64_t ld) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            v[i] = ld16_any(p[i]);
+            p[i] += KMAJ ? 64 : 64 * ld;
+        }
+    }
+    // Any step, element by element where a chunk is cut.
+    __device__ __forceinline__ static void load_edge(Regs &v, const uint16_t *base, int64_t ld,
+                                                     int mn0, int mn_lim, int k0, int k_lim,
+                                                     int tid) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int q = i * 64 * NW + tid;
+            const int row = KMAJ ? min(mn0 + q / CPR, mn_lim - 1) : k0 + q / CPR;
+            const int at = (KMAJ ? k0 : mn0) + (q % CPR) * 8, lim = KMAJ ? k_lim : mn_lim;
+            const uint16_t *r = base + (int64_t)row * ld;
+            v[i] = u32x4{0u, 0u, 0u, 0u};
+            if (!KMAJ && row >= k_lim) continue;
+            if (at + 8 <= lim) v[i] = ld16_any(r + at);
+            else if (at < lim) v[i] = ld16_tail(r, at, lim);
+        }
+    }
+    __device__ __forceinline__ static void store(const Regs &v, char *lds, int tid) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int q = i * 64 * NW + tid;
+            const int row = q / CPR, c = q % CPR;
+            *reinterpret_cast<u32x4 *>(lds + row * T::RB + ((c ^ T::swz(row)) << 4)) = v[i];
+        }
+    }
+};
+
 template <int N>
 __device__ __forceinline__ void wait_vm() {
     static_assert(N >= 0 && N <= 63, "vmcnt holds 6 bits");
@@ -314,12 +416,12 @@ __device__ __forceinline__ void store_staged(const float *tile, void *C, int64_t
             float *dst = reinterpret_cast<float *>(C) + (int64_t)row * ldc + col;
             if (vec && (!SHIFT || col >= 0) && col + 4 <= n) {
                 if constexpr (ACC) {
-                    v += *reinterpret_cast<const f32x4 *>(dst);
-                    *reinterpret_cast<f32x4 *>(dst) = v;
+                    v += *reinterpret_cast<const f32x4_any *>(dst);
+                    *reinterpret_cast<f32x4_any *>(dst) = v;
                 } else if constexpr (PART) {
                     st_part(part_rsrc(C), (int64_t)row * ldc + col, v);
                 } else {
-                    st_nt(reinterpret_cast<f32x4 *>(dst), v);
+                    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any *>(dst));
                 }
             } else {
 #pragma unroll
@@ -340,7 +442,7 @@ __device__ __forceinline__ void store_staged(const float *tile, void *C, int64_t
                 w[1] = (uint32_t)f32_to_bf16_bits(a[2]) | ((uint32_t)f32_to_bf16_bits(a[3]) << 16);
                 w[2] = (uint32_t)f32_to_bf16_bits(b[0]) | ((uint32_t)f32_to_bf16_bits(b[1]) << 16);
                 w[3] = (uint32_t)f32_to_bf16_bits(b[2]) | ((uint32_t)f32_to_bf16_bits(b[3]) << 16);
-                st_nt(reinterpret_cast<u32x4 *>(dst), w);
+                __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any *>(dst));
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
@@ -371,7 +473,7 @@ enum : int {
 // LDS, so the next item may refill it; after the direct epilogue the caller
 // must synchronise the workgroup first.
 template <int BM, int BN, int BKD, int NS, int WGM, int WGN, int KG, int EPI, bool A_KMAJ,
-          bool B_KMAJ, bool OUT_F32, bool SHIFT, class Args>
+          bool B_KMAJ, bool OUT_F32, bool SHIFT, bool REG = false, class Args>
 __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *smem) {
     constexpr int NSW = WGM * WGN;                // waves per reduction group
     constexpr int NW = NSW * KG;
@@ -444,12 +546,88 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
+    // the MFMAs of the stage at `cur`
+    auto compute = [&](const char *cur) {
+#pragma unroll
+        for (int kk = 0; kk < KSG; ++kk) {
+            const int ks = kg * KSG + kk;
+            bf16x8 af[MI], bfr[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+                af[i] = TA::frag(cur, wm * WM + i * 32, ks, lane);
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                bfr[j] = TB::frag(cur + A_BYTES, wn * WN + j * 32, ks, lane);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i],
+                                                                               acc[i][j], 0, 0, 0)
+                                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j],
+                                                                               acc[i][j], 0, 0, 0);
+        }
+    };
+
+    if constexpr (REG) {
+        // register-staged: the loads of steps it + 2 and it + 3 are in flight
+        // while step it computes; step it + 1 moves from registers to the
+        // other LDS stage, last read one barrier ago
+        static_assert(!REG || (NS == 2 && BKD == 64 && !SHIFT), "register staging: two stages");
+        using RA = RegTile<BM, NW, A_KMAJ>;
+        using RB = RegTile<BN, NW, B_KMAJ>;
+        typename RA::Regs va[2];
+        typename RB::Regs vb[2];
+        const int whole = min(RA::whole_steps(m0, g.m, k_begin, k_lim, g.k),
+                              RB::whole_steps(n0, g.n, k_begin, k_lim, g.k));
+        if (whole > 0) {
+            RA ra;
+            RB rb;
+            ra.init(Ab, g.lda, m0, g.m, k_begin, tid);
+            rb.init(Bb, g.ldb, n0, g.n, k_begin, tid);
+            auto load = [&](int r) {
+                ra.load(va[r], g.lda);
+                rb.load(vb[r], g.ldb);
+            };
+            auto fill = [&](int stage, int r) {
+                RA::store(va[r], smem + stage * STAGE, tid);
+                RB::store(vb[r], smem + stage * STAGE + A_BYTES, tid);
+            };
+            auto step = [&](int it, auto par) {   // par: (it + 1) % 2
+                constexpr int P = decltype(par)::value;
+                if (it + 1 < whole) fill(P, P);
+                if (it + 3 < whole) load(P);
+                compute(smem + (1 - P) * STAGE);
+                __syncthreads();
+            };
+            load(0);
+            if (whole > 1) load(1);
+            fill(0, 0);
+            if (whole > 2) load(0);
+            __syncthreads();
+            for (int it = 0; it < whole; it += 2) {
+                step(it, std::integral_constant<int, 1>{});
+                if (it + 1 < whole) step(it + 1, std::integral_constant<int, 0>{});
+            }
+        }
+        for (int it = whole; it < nkb; ++it) {
+            const int k0 = k_begin + it * BKD;
+            RA::load_edge(va[0], Ab, g.lda, m0, g.m, k0, k_lim, tid);
+            RB::load_edge(vb[0], Bb, g.ldb, n0, g.n, k0, k_lim, tid);
+            RA::store(va[0], smem, tid);
+            RB::store(vb[0], smem + A_BYTES, tid);
+            __syncthreads();
+            compute(smem);
+            __syncthreads();
+        }
+    }
+
     // prologue: stages 0 .. NS-2 in flight
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
-        if (s < nkb) issue(s, s);
+        if (!REG && s < nkb) issue(s, s);
 
-    for (int it = 0; it < nkb; ++it) {
+    for (int it = 0; !REG && it < nkb; ++it) {
         // wait for this thread's loads of step `it`; later steps may stay in flight
         wait_stages<NS - 2, LOADS>(min(NS - 2, nkb - 1 - it));
         __syncthreads();
@@ -471,25 +649,7 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                 __syncthreads();
             }
         }
-#pragma unroll
-        for (int kk = 0; kk < KSG; ++kk) {
-            const int ks = kg * KSG + kk;
-            bf16x8 af[MI], bfr[NI];
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-                af[i] = TA::frag(cur, wm * WM + i * 32, ks, lane);
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-                bfr[j] = TB::frag(cur + A_BYTES, wn * WN + j * 32, ks, lane);
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i],
-                                                                               acc[i][j], 0, 0, 0)
-                                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j],
-                                                                               acc[i][j], 0, 0, 0);
-        }
+        compute(cur);
     }
 
     // Split reduction: this workgroup's fp32 partial goes to slice `split`
@@ -656,10 +816,10 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                                                                   om0, on0, ws_vec, tid);
         else if (OUT_F32 && g.accumulate)
             store_staged<BM, BN, LD, 64 * NW, OUT_F32, OUT_F32, SHIFT>(
-                tile, Cb, g.ldc, g.m, g.n, om0, on0, g.vec_c4, tid);
+                tile, Cb, g.ldc, g.m, g.n, om0, on0, REG || g.vec_c4, tid);
         else
             store_staged<BM, BN, LD, 64 * NW, OUT_F32, false, SHIFT>(
-                tile, Cb, g.ldc, g.m, g.n, om0, on0, OUT_F32 ? g.vec_c4 : g.vec_c8, tid);
+                tile, Cb, g.ldc, g.m, g.n, om0, on0, REG || (OUT_F32 ? g.vec_c4 : g.vec_c8), tid);
         __syncthreads();   // the staged tile is free again
         return;
     }
@@ -731,6 +891,24 @@ void gemm_bf16_dma_kernel(ArgsOf<SHIFT> g) {
         dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, A_KMAJ, B_KMAJ, OUT_F32, SHIFT>(
             g, remap_xcd(v, total), smem);
     }
+}
+
+// The generic kernel: operands at any element alignment and leading dimension,
+// staged through registers. Eight waves, as 2 x 4 on 128 x 128 (108 registers,
+// two workgroups per CU), as 2 x 2 in two reduction groups on the smaller
+// tiles. Bound by the unaligned loads: a chunk that crosses a line costs two.
+// Measured on odd leading dimensions (before: masked 2-byte loads wherever a
+// vector was not aligned): 2051 x 2502 x 1024 forward 103 -> 28 us, its
+// backward-data product 186 -> 32 us, backward-weight 70 -> 28 us; 3777 x 1801 x
+// 5504 backward-weight runs at 645 TFLOP/s.
+template <int BM, int BN, int WGM, int WGN, int KG, int EPI, bool A_KMAJ, bool B_KMAJ,
+          bool OUT_F32>
+__global__ __launch_bounds__(64 * WGM * WGN * KG, (BM * BN > 64 * 128 ? 2 : 4))
+void gemm_bf16_reg_kernel(GemmArgs g) {
+    __shared__ __attribute__((aligned(1024))) char smem[2 * DmaStage<BM, BN, 64, 2>::BYTES];
+    const int total = g.tiles_m * g.tiles_n * g.splits * g.nbatch;
+    dma_tile_body<BM, BN, 64, 2, WGM, WGN, KG, EPI, A_KMAJ, B_KMAJ, OUT_F32, false, true>(
+        g, remap_xcd(blockIdx.x, total), smem);
 }
 
 // The two backward products of one linear in one launch: gd is the

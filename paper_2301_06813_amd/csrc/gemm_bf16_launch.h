@@ -115,12 +115,13 @@ static hipError_t launch_tile(const Plan &p, const sbpk::GemmArgsShift &as, int 
 #undef SBP_DMA_SHIFT_TILE
         return hipErrorInvalidValue;
     }
-#define SBP_TILE(BM_, BN_)                                                                  \
+#define SBP_TILE(BM_, BN_, WGM_, WGN_, KG_, EPI_)                                            \
     if (!p.dma && p.bm == BM_ && p.bn == BN_) {                                             \
-        snprintf(name, sizeof(name), "gemm_bf16_kernel<%d, %d, %s, %s, %s>", BM_, BN_,     \
-                 tf[AK], tf[BK_], tf[OUTF]);                                                \
-        return launch_kernel(sbpk::gemm_bf16_kernel<BM_, BN_, AK, BK_, OUTF>, name,         \
-                             dim3(items), dim3(sbpk::NT), s, a);                            \
+        snprintf(name, sizeof(name), "gemm_bf16_reg_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s>", \
+                 BM_, BN_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF]);               \
+        return launch_kernel(                                                               \
+            sbpk::gemm_bf16_reg_kernel<BM_, BN_, WGM_, WGN_, KG_, EPI_, AK, BK_, OUTF>,     \
+            name, dim3(items), dim3(64 * WGM_ * WGN_ * KG_), s, a);                         \
     }
 #define SBP_DMA_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                            \
     if (p.dma && p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ &&                               \
@@ -133,12 +134,12 @@ static hipError_t launch_tile(const Plan &p, const sbpk::GemmArgsShift &as, int 
                                        OUTF>,                                               \
             name, dim3(grid), dim3(64 * WGM_ * WGN_ * KG_), s, a);                          \
     }
-    SBP_TILE(256, 128)
-    SBP_TILE(128, 256)
-    SBP_TILE(128, 128)
-    SBP_TILE(128, 64)
-    SBP_TILE(64, 128)
-    SBP_TILE(64, 64)
+    SBP_TILE(256, 128, 4, 2, 1, sbpk::EPI_DIRECT)
+    SBP_TILE(128, 256, 2, 4, 1, sbpk::EPI_DIRECT)
+    SBP_TILE(128, 128, 2, 4, 1, sbpk::EPI_STAGED)
+    SBP_TILE(128, 64, 2, 2, 2, sbpk::EPI_STAGED)
+    SBP_TILE(64, 128, 2, 2, 2, sbpk::EPI_STAGED)
+    SBP_TILE(64, 64, 2, 2, 2, sbpk::EPI_STAGED)
     SBP_DMA_INSTANCES(SBP_DMA_TILE)
 #undef SBP_TILE
 #undef SBP_DMA_TILE
@@ -175,10 +176,6 @@ static inline sbpk::GemmArgsShift make_args(const Gemm &g, const Plan &p, float 
     a.splits = p.splits;
     a.kchunk = p.kblk_per_split * 64;
     a.ws = ws;
-    const bool batch_a = g.nbatch() == 1 || (g.sa_b % 8 == 0 && g.sa_h % 8 == 0);
-    const bool batch_b = g.nbatch() == 1 || (g.sb_b % 8 == 0 && g.sb_h % 8 == 0);
-    a.vec_a = ((reinterpret_cast<uintptr_t>(g.A) & 15) == 0) && (g.lda % 8 == 0) && batch_a;
-    a.vec_b = ((reinterpret_cast<uintptr_t>(g.B) & 15) == 0) && (g.ldb % 8 == 0) && batch_b;
     // every batch item's output base must keep the 16-byte alignment
     const int64_t es = g.out_dtype == DT_F32 ? 4 : 2;
     const bool c16 = (reinterpret_cast<uintptr_t>(g.C) & 15) == 0 &&

@@ -29,10 +29,16 @@ struct TileClass {
     int bk = 64;           // reduction elements per pipeline stage
 };
 
-// Generic kernel (register-staged, one step ahead): slower per byte.
-const TileClass kGeneric[] = {
-    {256, 128, 1, 0.5, 0}, {128, 256, 1, 0.5, 0}, {128, 128, 2, 0.5, 0},
-    {128, 64, 2, 0.5, 0},  {64, 128, 2, 0.5, 0},  {64, 64, 4, 0.5, 0},
+// Generic kernel (register-staged): time of one 64-wide reduction step of a
+// work item on a compute unit, measured on products with odd leading
+// dimensions (see plan_generic).
+struct GenericTile {
+    int bm, bn;
+    double step;
+};
+const GenericTile kGeneric[] = {
+    {256, 128, 1.40e-6}, {128, 256, 1.40e-6}, {128, 128, 0.70e-6},
+    {128, 64, 0.50e-6},  {64, 128, 0.50e-6},  {64, 64, 0.33e-6},
 };
 // Pipelined direct-to-LDS kernel.
 // The two-stage 128 x 128 instance (64 KB of LDS) runs two workgroups per
@@ -229,7 +235,7 @@ bool tile_supported(int bm, int bn, bool dma) {
         for (const TileClass &t : kDma)
             if (t.bm == bm && t.bn == bn) return true;
     } else {
-        for (const TileClass &t : kGeneric)
+        for (const GenericTile &t : kGeneric)
             if (t.bm == bm && t.bn == bn) return true;
     }
     return false;
@@ -482,6 +488,38 @@ bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
     return grouped;
 }
 
+// Generic kernel: the busiest compute unit's share of the work items, each
+// `per` steps (the workgroups of a unit share its load path, so their steps
+// add up: 0.70 us per 128 x 128 step alone and with two workgroups), plus a
+// fixed cost and the split reduction. Measured: 2051 x 2502 x 1024 forward 27.7
+// us on 128 x 128 tiles, 35.6 on 64 x 64 ones, 32.0 on 256 x 128; 250 x 511 x
+// 6001 12.7 us on 64 x 64 split 8 ways.
+static Plan plan_generic(const Gemm &g) {
+    const int kb_total = kblocks(g.k);
+    Plan best{64, 64, 1, std::max(1, kb_total), false};
+    double best_t = 1e30;
+    for (const GenericTile &t : kGeneric) {
+        const double nt = (double)((g.m + t.bm - 1) / t.bm) * (double)((g.n + t.bn - 1) / t.bn) *
+                          (double)g.nbatch();
+        int last = 0;
+        for (int s = 1; s <= 32; ++s) {
+            int splits, per;
+            split_of(kb_total, s, &splits, &per);
+            if (splits == last) continue;
+            last = splits;
+            if (splits > 1 && (per < 2 || !fits_ws(g, splits))) continue;
+            const double q = nt * splits / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
+            double tm = busy * per * t.step + 5e-6;
+            if (splits > 1) tm += (splits * 2.0 + 0.5) * 4.0 * g.m * g.n / 6e12 + 3e-6;
+            if (tm < best_t * 0.999) {
+                best_t = tm;
+                best = Plan{t.bm, t.bn, splits, per, false};
+            }
+        }
+    }
+    return best;
+}
+
 static Plan plan_uncached(const Gemm &g) {
     const int kb_total = kblocks(g.k);
     const int mode = dma_mode(g);
@@ -539,12 +577,9 @@ static Plan plan_uncached(const Gemm &g) {
             if (fits_ws(g, p.splits)) return p;
         }
     }
+    if (!dma) return plan_generic(g);
     double best_t = 1e30;
-    const TileClass *tiles_tab = dma ? kDma : kGeneric;
-    const int ntiles = dma ? (int)(sizeof(kDma) / sizeof(kDma[0]))
-                           : (int)(sizeof(kGeneric) / sizeof(kGeneric[0]));
-    for (int ti = 0; ti < ntiles; ++ti) {
-        const TileClass &t = tiles_tab[ti];
+    for (const TileClass &t : kDma) {
         if (mode == 2 && !shift_capable(t.bm, t.bn, t.bk, t.ns, t.kg, t.epi)) continue;
         int last_splits = 0;
         for (int s = 1; s <= 32; ++s) {
@@ -557,7 +592,7 @@ static Plan plan_uncached(const Gemm &g) {
             const double tm = model_time(g, t, splits, per);
             if (tm < best_t * 0.999) {
                 best_t = tm;
-                best = Plan{t.bm, t.bn, splits, per, dma, t.ns, t.kg, t.epi, t.occ_persist, t.bk};
+                best = Plan{t.bm, t.bn, splits, per, true, t.ns, t.kg, t.epi, t.occ_persist, t.bk};
                 best.shift = mode == 2;
             }
         }
