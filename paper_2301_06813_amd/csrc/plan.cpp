@@ -18,17 +18,6 @@ namespace sbpi {
 
 namespace {
 
-struct TileClass {
-    int bm, bn;
-    int occ;      // workgroups that fit one compute unit (LDS-limited)
-    double eff;   // rate factor of the tile's operand stream (see model below)
-    int ns;       // pipelined kernel stages (0 = default instance)
-    int kg = 1;   // pipelined kernel reduction groups (2: eight waves)
-    int epi = 0;  // pipelined kernel epilogue
-    int occ_persist = 0;   // persistent workgroups per CU (0: one per item)
-    int bk = 64;           // reduction elements per pipeline stage
-};
-
 // Generic kernel (register-staged): time of one 64-wide reduction step of a
 // work item on a compute unit, measured on products with odd leading
 // dimensions (see plan_generic).
@@ -40,31 +29,36 @@ const GenericTile kGeneric[] = {
     {256, 128, 1.40e-6}, {128, 256, 1.40e-6}, {128, 128, 0.70e-6},
     {128, 64, 0.50e-6},  {64, 128, 0.50e-6},  {64, 64, 0.33e-6},
 };
-// Pipelined direct-to-LDS kernel.
-// The two-stage 128 x 128 instance (64 KB of LDS) runs two workgroups per
-// CU: one's output stores overlap the other's loads, which pays off when the
-// reduction is short and the output large.
-// The 128-wide stages with two reduction groups (one workgroup of eight
-// waves per CU) stream their operands about 20 % faster per CU.
-const TileClass kDma[] = {
-    {256, 256, 1, 1.0, 0}, {256, 192, 1, 1.0, 0},
-    {256, 128, 1, 1.0, 0}, {128, 256, 1, 1.0, 0}, {128, 128, 1, 1.0, 0},
-    {128, 128, 2, 0.8, 2}, {128, 64, 1, 1.0, 0},  {64, 128, 1, 1.0, 0},  {64, 64, 2, 1.0, 0},
-    {128, 128, 1, 1.2, 2, 2, 1, 0, 128}, {128, 64, 1, 1.2, 3, 2, 1, 0, 128},
-    {64, 128, 1, 1.2, 3, 2, 1, 0, 128},  {64, 64, 1, 1.2, 4, 2, 1, 0, 128},
+// Pipelined instances the model chooses among, with their measured times on
+// MI355X in us: a 64-wide reduction step of a work item alone on its compute
+// unit (`step[0]`), its share of the unit when two workgroups take turns there
+// (`step[1]`) and when three or more do (`step[2]`; `res` at most), and the
+// store of an fp32 output tile (`epi`; half for bf16). Fitted to 23 instances
+// x every split on 438 random products and 176 random backward pairs (extents
+// of 64 to 8192; 3 % rms); the instances left out were the fastest for almost
+// none of them. Over those the plans chosen take 3 % longer than the fastest
+// measured (products) and 4 % (pairs); the model of peak rates before this one
+// chose plans 8 % and 27 % longer.
+struct PipeClass {
+    int bm, bn, code, res;
+    double step[3], epi;
+};
+const PipeClass kPipe[] = {
+    {64, 64, 1, 2, {0.336, 0.210, 0.210}, 0.86},    {64, 64, 4, 5, {0.385, 0.264, 0.188}, 0.57},
+    {64, 64, 12, 1, {0.203, 0.203, 0.203}, 2.09},   {64, 128, 4, 3, {0.530, 0.323, 0.282}, 1.04},
+    {64, 128, 12, 1, {0.347, 0.347, 0.347}, 2.75},  {128, 64, 4, 3, {0.530, 0.323, 0.282}, 1.04},
+    {128, 64, 12, 1, {0.347, 0.347, 0.347}, 2.75},  {128, 128, 4, 2, {0.667, 0.422, 0.422}, 2.06},
+    {128, 128, 12, 1, {0.505, 0.505, 0.505}, 3.78}, {256, 192, 1, 1, {1.186, 1.186, 1.186}, 4.01},
+    {256, 256, 1, 1, {1.558, 1.558, 1.558}, 4.31},
 };
 
-// Time model (measured on MI355X): a workgroup's 64-wide reduction step
-// costs the larger of its MFMA time and its operand bytes over the per-CU
-// share of L2->LDS bandwidth (about 10 TB/s over 256 CUs when all are busy);
-// `eff` scales that rate per kernel. Each wave of workgroups pays a fixed
-// latency; split reductions pay their fp32 partials and the reduce kernel.
 constexpr double kCUs = 256.0;
-constexpr double kCuPeak = 4096.0 * 2.4e9;      // bf16 flop/s per CU
-constexpr double kCuL2 = 40.0e9;                // L2 -> LDS bytes/s per CU, chip busy
-constexpr double kHbm = 5.0e12;                 // sustained HBM bytes/s (mixed read/write)
-constexpr double kRoundLatency = 2.0e-6;        // pipeline fill + epilogue per wave
-constexpr double kLaunch = 2.0e-6;              // extra launch (reduce kernel)
+constexpr double kFixed = 5.2;         // launch, first loads, last stores (us)
+constexpr double kHbm = 5.6e6;         // bytes per us of a product that streams (mixed)
+constexpr double kReduce = 0.88;       // the split reduction's launch (us), ...
+constexpr double kReduceLoads = 0.32;  // each four slices it reads one after another
+constexpr double kReduceRate = 5.40e6; // and its bytes per us, partials written and read
+constexpr double kKmajor = 0.965;     // step time with both operands k-major
 
 thread_local int ov_bm = 0, ov_bn = 0, ov_splits = 1, ov_kernel = 0, ov_occ = 0;
 thread_local int ov_orients = 7;   // orientations the override applies to (bit per Orient)
@@ -182,58 +176,72 @@ bool fits_ws(const Gemm &g, int splits) {
     return (double)splits * (double)g.m * (double)partial_ld(g.n) <= ws_budget(g);
 }
 
-// Work items of one product under (tile, splits): count, time per item, and
-// the cost of its split reduction (0 without splits).
-struct Est {
-    double wgs, wg_time, extra;
-};
-
-Est estimate(const Gemm &g, const TileClass &t, int splits, int per) {
-    const int64_t tiles = ((g.m + t.bm - 1) / t.bm) * ((g.n + t.bn - 1) / t.bn) * g.nbatch();
-    const double step_bytes = (t.bm + t.bn) * 128.0;
-    const double step = std::max(2.0 * t.bm * t.bn * 64.0 / (kCuPeak * 0.9),
-                                 step_bytes * t.occ / (kCuL2 * t.eff));
-    const double out_bytes = (splits > 1 || g.out_dtype == DT_F32) ? 4.0 : 2.0;
-    // output stores overlap other workgroups' loads when two share a CU
-    const double epi = t.bm * t.bn * out_bytes / kCuL2 / t.occ;
-    Est e{(double)tiles * splits, per * step + epi + kRoundLatency / t.occ, 0.0};
-    if (splits > 1) {
-        const double red = (splits * 4.0 + ((g.out_dtype == DT_F32) ? 4.0 : 2.0)) * g.m * g.n;
-        e.extra = red / kHbm + kLaunch;
-    }
-    return e;
-}
+double out_elem(const Gemm &g) { return g.out_dtype == DT_F32 ? 4.0 : 2.0; }
 
 double algo_bytes(const Gemm &g) {
-    return (2.0 * (g.m * g.k + g.k * g.n) + ((g.out_dtype == DT_F32) ? 4.0 : 2.0) * g.m * g.n) *
+    return (2.0 * ((double)g.m * g.k + (double)g.k * g.n) + out_elem(g) * g.m * g.n) *
            (double)g.nbatch();
 }
 
-double model_time(const Gemm &g, const TileClass &t, int splits, int per) {
-    const Est e = estimate(g, t, splits, per);
-    const double rounds = std::ceil(e.wgs / (kCUs * t.occ));
-    return std::max(rounds * e.wg_time, algo_bytes(g) / kHbm) + e.extra;
+double step_of(const PipeClass &c, double r) { return c.step[r > 2.0 ? 2 : r > 1.0 ? 1 : 0]; }
+
+// Work items of a product under class c: their number, one's reduction steps
+// (in units of an n-major step) and the time of its stores.
+struct Items {
+    double n, steps, epi;
+};
+Items items_of(const Gemm &g, const PipeClass &c, int splits, int per) {
+    const double tiles = (double)((g.m + c.bm - 1) / c.bm) * (double)((g.n + c.bn - 1) / c.bn);
+    return {tiles * splits * (double)g.nbatch(),
+            per * (g.orient == OR_BWD_DATA ? kKmajor : 1.0),
+            c.epi * (splits > 1 ? 1.0 : out_elem(g) / 4.0)};
+}
+double reduce_time(const Gemm &g, int splits) {
+    return splits > 1 ? (4.0 * splits + out_elem(g)) * g.m * g.n / kReduceRate : 0.0;
+}
+
+double reduce_loads(int splits) { return kReduceLoads * ((splits + 3) / 4); }
+
+// One product: the busiest unit's items in turn (beyond four the units even
+// out), not faster than its bytes, then the split reduction.
+double model_time(const Gemm &g, const PipeClass &c, int splits, int per) {
+    const Items i = items_of(g, c, splits, per);
+    const double q = i.n / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
+    const double r = std::min((double)c.res, std::ceil(q));
+    const double t = busy * (i.steps * step_of(c, r) + i.epi);
+    return kFixed + std::max(t, algo_bytes(g) / kHbm) +
+           (splits > 1 ? kReduce + reduce_loads(splits) + reduce_time(g, splits) : 0.0);
 }
 
 // Two products sharing one grid: the longer items are dispatched first and
-// the shorter fill in behind them.
-double model_pair(const Gemm &gd, const Gemm &gw, const TileClass &t, int sd, int pd, int sw,
+// the shorter fill in behind them. The whole lasts at least as long as the
+// even share of a unit plus 0.6 of a short item, and as one long item, whose
+// steps wait for the other workgroups of its unit (0.7 of taking turns with all
+// of them to the end: they finish sooner).
+double model_pair(const Gemm &gd, const Gemm &gw, const PipeClass &c, int sd, int pd, int sw,
                   int pw) {
-    const Est a = estimate(gd, t, sd, pd), b = estimate(gw, t, sw, pw);
-    const Est &lo = (a.wg_time >= b.wg_time) ? a : b;
-    const Est &sh = (a.wg_time >= b.wg_time) ? b : a;
-    const double slots = kCUs * t.occ;
-    const double total = lo.wgs * lo.wg_time + sh.wgs * sh.wg_time;
-    const double mk = std::max(std::ceil(lo.wgs / slots) * lo.wg_time, total / slots + sh.wg_time);
-    return std::max(mk, (algo_bytes(gd) + algo_bytes(gw)) / kHbm) + a.extra + b.extra;
+    const Items d = items_of(gd, c, sd, pd), w = items_of(gw, c, sw, pw);
+    const double q = (d.n + w.n) / kCUs, r = std::min((double)c.res, std::ceil(q));
+    const double step = step_of(c, r);
+    const double cd = d.steps * step + d.epi, cw = w.steps * step + w.epi;
+    const bool data_first = pd >= pw;
+    const double n1 = data_first ? d.n : w.n, c1 = data_first ? cd : cw;
+    const double c2 = data_first ? cw : cd;
+    double t = std::max(c1, c2);
+    if (q > 1.0)
+        t = std::max(std::ceil(n1 / kCUs) * c1, (d.n * cd + w.n * cw) / kCUs + 0.6 * c2);
+    const double wait = std::max(c.step[0], r > 1.0 ? 0.7 * r * step : 0.0);
+    t = std::max(t, std::max(d.steps * wait + d.epi, w.steps * wait + w.epi));
+    return kFixed + std::max(t, (algo_bytes(gd) + algo_bytes(gw)) / kHbm) +
+           (sd > 1 || sw > 1 ? kReduce + reduce_loads(std::max(sd, sw)) : 0.0) +
+           reduce_time(gd, sd) + reduce_time(gw, sw);
 }
 
 }  // namespace
 
 bool tile_supported(int bm, int bn, bool dma) {
     if (dma) {
-        for (const TileClass &t : kDma)
-            if (t.bm == bm && t.bn == bn) return true;
+        return find_instance(1, bm, bn) != nullptr;
     } else {
         for (const GenericTile &t : kGeneric)
             if (t.bm == bm && t.bn == bn) return true;
@@ -310,6 +318,7 @@ int dma_mode(const Gemm &g) {
 }
 
 static Plan plan_uncached(const Gemm &g);
+static Plan plan_model(const Gemm &g, double *time);
 
 // Tuned entry of product g under pipelined-kernel mode `mode` (nullptr if none).
 static const Tuned *tuned_for(const Gemm &g, int mode) {
@@ -360,16 +369,40 @@ Key key_of(const Gemm &g, int mode) {
                 g.nbatch(), (int64_t)std::min(g.ws_floats, WS_FLOATS_PREFERRED)}};
 }
 thread_local std::unordered_map<Key, Plan, KeyHash> plan_cache;
+
+struct PairKey {
+    Key d, w;
+    int64_t bwd;   // the backward override
+    bool operator==(const PairKey &o) const { return d == o.d && w == o.w && bwd == o.bwd; }
+};
+struct PairHash {
+    size_t operator()(const PairKey &k) const {
+        return (KeyHash()(k.d) * 31 + KeyHash()(k.w)) * 31 + (size_t)k.bwd;
+    }
+};
+struct PairPlan {
+    bool grouped;
+    Plan d, w;
+};
+thread_local std::unordered_map<PairKey, PairPlan, PairHash> pair_cache;
 }  // namespace
 
-Plan plan_bf16(const Gemm &g) {
-    const Key k = key_of(g, dma_mode(g));
+static Plan plan_f32_uncached(const Gemm &g, bool big_ld);
+
+static const Plan &cached_plan(const Gemm &g, int mode) {
+    const Key k = key_of(g, mode);
     auto it = plan_cache.find(k);
     if (it != plan_cache.end()) return it->second;
-    const Plan p = plan_uncached(g);
+    const Plan p = g.in_dtype == DT_F32 ? plan_f32_uncached(g, mode != 0) : plan_uncached(g);
     if (plan_cache.size() > 4096) plan_cache.clear();
-    plan_cache.emplace(k, p);
-    return p;
+    return plan_cache.emplace(k, p).first->second;
+}
+
+Plan plan_bf16(const Gemm &g) { return cached_plan(g, dma_mode(g)); }
+
+Plan plan_f32(const Gemm &g) {
+    constexpr int64_t kMaxLd = int64_t(1) << 21;   // tile offsets stay below 2^31 bytes
+    return cached_plan(g, g.lda > kMaxLd || g.ldb > kMaxLd);
 }
 
 // Grouped plan of both products on instance `in` (tile bm x bn) with the
@@ -392,7 +425,7 @@ size_t plan_ws_floats(const Gemm &g, const Plan &p) {
     return p.splits > 1 ? (size_t)p.splits * (size_t)g.m * (size_t)partial_ld(g.n) : 0;
 }
 
-bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
+static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
     if (gd.nbatch() > 1 || gw.nbatch() > 1) {   // batched products run one by one
         *pd = plan_bf16(gd);
         *pw = plan_bf16(gw);
@@ -441,22 +474,15 @@ bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
         return (double)plan_ws_floats(gd, *pd) + (double)plan_ws_floats(gw, *pw) <=
                ws_budget(gd);
     }
-    const TileClass *sep_d = nullptr, *sep_w = nullptr;
-    for (const TileClass &t : kDma) {
-        if (t.bm == pd->bm && t.bn == pd->bn && t.ns == pd->ns && t.kg == pd->kg &&
-            t.epi == pd->epi && t.bk == pd->bk)
-            sep_d = &t;
-        if (t.bm == pw->bm && t.bn == pw->bn && t.ns == pw->ns && t.kg == pw->kg &&
-            t.epi == pw->epi && t.bk == pw->bk)
-            sep_w = &t;
-    }
-    if (!sep_d || !sep_w) return false;
-    double best = model_time(gd, *sep_d, pd->splits, pd->kblk_per_split) +
-                  model_time(gw, *sep_w, pw->splits, pw->kblk_per_split);
+    // grouped where the model expects it to beat the two products in turn
+    double best_d, best_w;
+    plan_model(gd, &best_d);
+    plan_model(gw, &best_w);
+    double best = best_d + best_w;
     bool grouped = false;
     const int kd = kblocks(gd.k), kw = kblocks(gw.k);
-    for (const TileClass &t : kDma) {
-        if (sh && !shift_capable(t.bm, t.bn, t.bk, t.ns, t.kg, t.epi)) continue;
+    for (const PipeClass &c : kPipe) {
+        const Instance &in = *find_instance(c.code, c.bm, c.bn);
         int last_d = 0;
         for (int a = 1; a <= 16; ++a) {
             int sd, perd;
@@ -471,21 +497,35 @@ bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
                 if (sw == last_w) continue;
                 last_w = sw;
                 if (sw > 1 && perw < 2) continue;
-                const double wsz = (sd > 1 ? (double)sd * gd.m * gd.n : 0.0) +
-                                   (sw > 1 ? (double)sw * gw.m * gw.n : 0.0);
-                if (wsz > ws_budget(gd)) continue;
-                const double tm = model_pair(gd, gw, t, sd, perd, sw, perw);
-                if (tm < best * 0.97) {
-                    best = tm;
-                    grouped = true;
-                    *pd = Plan{t.bm, t.bn, sd, perd, true, t.ns, t.kg, t.epi, 0, t.bk};
-                    *pw = Plan{t.bm, t.bn, sw, perw, true, t.ns, t.kg, t.epi, 0, t.bk};
-                    pd->shift = pw->shift = sh;
-                }
+                const double tm = model_pair(gd, gw, c, sd, perd, sw, perw);
+                if (tm >= best * 0.999) continue;
+                Plan qd, qw;
+                if (!grouped_plan(gd, gw, &in, c.bm, c.bn, sd, sw, &qd, &qw)) continue;
+                best = tm;
+                grouped = true;
+                *pd = qd;
+                *pw = qw;
             }
         }
     }
     return grouped;
+}
+
+// Plans are pure functions of the key, kept per thread so that a repeated
+// call does not search again (a pair weighs some 2,000 candidates).
+bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
+    const PairKey k{key_of(gd, dma_mode(gd)), key_of(gw, dma_mode(gw)),
+                    ov_bwd_mode * 65536 + ov_bwd_splits_w};
+    auto it = pair_cache.find(k);
+    if (it == pair_cache.end()) {
+        PairPlan p;
+        p.grouped = plan_bwd_uncached(gd, gw, &p.d, &p.w);
+        if (pair_cache.size() > 4096) pair_cache.clear();
+        it = pair_cache.emplace(k, p).first;
+    }
+    *pd = it->second.d;
+    *pw = it->second.w;
+    return it->second.grouped;
 }
 
 // Generic kernel: the busiest compute unit's share of the work items, each
@@ -524,11 +564,6 @@ static Plan plan_uncached(const Gemm &g) {
     const int kb_total = kblocks(g.k);
     const int mode = dma_mode(g);
     const bool dma = mode > 0;
-    Plan best{128, 128, 1, std::max(1, kb_total), dma};
-    if (mode == 2) {
-        best.ns = 2;   // the two-stage 128 x 128 instance has a shifted form
-        best.shift = true;
-    }
     if (ov_bm != 0 && ((ov_orients >> g.orient) & 1)) {
         // kernel: 0 or 1 the tile's default pipelined instance (if eligible),
         // 2 generic, other codes the instance of kInstances (if eligible);
@@ -577,10 +612,20 @@ static Plan plan_uncached(const Gemm &g) {
             if (fits_ws(g, p.splits)) return p;
         }
     }
-    if (!dma) return plan_generic(g);
-    double best_t = 1e30;
-    for (const TileClass &t : kDma) {
-        if (mode == 2 && !shift_capable(t.bm, t.bn, t.bk, t.ns, t.kg, t.epi)) continue;
+    double t;
+    return dma ? plan_model(g, &t) : plan_generic(g);
+}
+
+// The pipelined plan the model expects to be fastest, and its time in us.
+static Plan plan_model(const Gemm &g, double *time) {
+    const int kb_total = kblocks(g.k);
+    const bool shift = dma_mode(g) == 2;
+    Plan best{64, 64, 1, std::max(1, kb_total), true};
+    best.shift = shift;
+    *time = 1e30;
+    for (const PipeClass &c : kPipe) {
+        const Instance &in = *find_instance(c.code, c.bm, c.bn);
+        if (shift && !shift_capable(c.bm, c.bn, in.bk, in.ns, in.kg, in.epi)) continue;
         int last_splits = 0;
         for (int s = 1; s <= 32; ++s) {
             int splits, per;
@@ -589,11 +634,11 @@ static Plan plan_uncached(const Gemm &g) {
             last_splits = splits;
             if (splits > 1 && per < 2) continue;            // keep >= 128 reduction per split
             if (!fits_ws(g, splits)) continue;
-            const double tm = model_time(g, t, splits, per);
-            if (tm < best_t * 0.999) {
-                best_t = tm;
-                best = Plan{t.bm, t.bn, splits, per, true, t.ns, t.kg, t.epi, t.occ_persist, t.bk};
-                best.shift = mode == 2;
+            const double tm = model_time(g, c, splits, per);
+            if (tm < *time * 0.999) {
+                *time = tm;
+                best = Plan{c.bm, c.bn, splits, per, true, in.ns, in.kg, in.epi, 0, in.bk};
+                best.shift = shift;
             }
         }
     }
@@ -608,12 +653,11 @@ static Plan plan_uncached(const Gemm &g) {
 // several 64 x 64 workgroups (1024 x 1024 x 4096: 98 us unsplit, 79 us split
 // four ways), and outputs of a whole wave of 128 x 128 tiles take those
 // (4096^3: 1028 us against 1068 us; 1024 x 4096 x 1024: 75 us for both).
-Plan plan_f32(const Gemm &g) {
-    constexpr int64_t kMaxLd = int64_t(1) << 21;   // tile offsets stay below 2^31 bytes
+static Plan plan_f32_uncached(const Gemm &g, bool big_ld) {
     const int kb = (int)((g.k + 31) / 32);
     Plan best{64, 64, 1, std::max(1, kb), false};
     best.bk = 32;
-    if (g.lda > kMaxLd || g.ldb > kMaxLd) return best;   // plain FMA kernel
+    if (big_ld) return best;   // plain FMA kernel
     best.dma = true;
     double best_t = 1e30;
     for (const int t : {64, 128}) {

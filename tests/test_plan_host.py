@@ -1,0 +1,57 @@
+"""Plans chosen by the time model: valid over a range of shapes, a pure
+function of the product (kept plans do not outlive an override), and grouped
+backward plans whose partials fit the workspace."""
+import random
+
+import pytest
+
+from paper_2301_06813_amd import sbp
+
+BF, F32 = sbp.SBP_BF16, sbp.SBP_F32
+TILES = {(256, 256), (256, 192), (256, 128), (128, 256), (128, 128), (128, 64), (64, 128),
+         (64, 64)}
+
+
+def _extent(rng):
+    v = round(2 ** rng.uniform(0, 13))
+    return max(1, v // 64 * 64) if rng.random() < 0.5 else v
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_plans_are_valid_and_repeat(seed):
+    rng = random.Random(seed)
+    for _ in range(100):
+        m, n, k = (_extent(rng) for _ in range(3))
+        for op in range(3):
+            for din, dout in ((BF, BF), (BF, F32), (F32, F32)):
+                tm, tn, splits, kernel = p = sbp.sbp_plan(op, m, n, k, din, dout)
+                assert (tm, tn) in TILES and 1 <= splits <= 32
+                assert kernel == sbp.KERNEL_F32 if din == F32 else kernel != sbp.KERNEL_F32
+                block = 32 if din == F32 else 64
+                assert splits == 1 or (splits - 1) * block < k
+                ld = -(-n // 4) * 4
+                assert splits == 1 or 4 * splits * m * ld <= sbp.SBP_WORKSPACE_BYTES
+                assert sbp.sbp_plan(op, m, n, k, din, dout) == p
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_backward_pair_plans_fit_and_follow_overrides(seed):
+    rng = random.Random(100 + seed)
+    for _ in range(30):
+        M, K, N = (_extent(rng) for _ in range(3))
+        fd, fw = rng.choice(((BF, F32), (F32, BF), (F32, F32)))
+        args = (M, K, N, fd, K, N, M, fw)
+        grouped, tm, tn, sd, sw = p = sbp.sbp_plan_bwd(*args)
+        assert (tm, tn) in TILES
+        if grouped:
+            part = [4 * s * r * (-(-c // 4) * 4) if s > 1 else 0
+                    for s, r, c in ((sd, M, K), (sw, K, N))]
+            assert sum(part) <= sbp.SBP_WORKSPACE_BYTES
+        try:
+            sbp.sbp_set_plan_override(64, 64, 1, 1)
+            sbp.sbp_set_bwd_override(2, 1)
+            q = sbp.sbp_plan_bwd(*args)
+            assert q[1:] == (64, 64, 1, 1) or not q[0]
+        finally:
+            sbp.sbp_set_plan_override(0, 0, 1)
+        assert sbp.sbp_plan_bwd(*args) == p
