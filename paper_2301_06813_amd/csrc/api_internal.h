@@ -11,5 +11,7 @@ namespace sbpa {
 // inputs) on stream s; SBP_OK, or SBP_ERR_HIP with the HIP error recorded
 // for sbp_last_hip_error(). An empty product launches nothing.
 int run_gemm(const sbpi::Gemm &g, hipStream_t s);
+// Two independent products (a backward pair) in one launch or in turn.
+int run_gemm_pair(const sbpi::Gemm &gd, const sbpi::Gemm &gw, hipStream_t s);
 
 }  // namespace sbpa

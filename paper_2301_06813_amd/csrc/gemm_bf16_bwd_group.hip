@@ -4,6 +4,12 @@
 
 namespace sbpi {
 
+// Grouped launch of a forward-orientation and a backward-weight product
+// (gemm_bf16_attn_group.hip), both with fp32 or both with bf16 outputs.
+hipError_t launch_pair_fwd_weight(bool f32, const Plan &p, const sbpk::GemmArgs &d,
+                                  const sbpk::GemmArgs &w, int data_first, int grid,
+                                  hipStream_t s);
+
 namespace {
 
 template <bool OD, bool OW>
@@ -55,11 +61,16 @@ hipError_t launch_bf16_bwd_group(const Gemm &gd, const Plan &pd, const Gemm &gw,
     float *const ws_w = ws + plan_ws_floats(gd, pd);
     const sbpk::GemmArgsShift d = make_args(gd, pd, ws);
     const sbpk::GemmArgsShift w = make_args(gw, pw, ws_w);
-    const int grid = d.tiles_m * d.tiles_n * d.splits + w.tiles_m * w.tiles_n * w.splits;
+    const int grid = d.tiles_m * d.tiles_n * d.splits * d.nbatch +
+                     w.tiles_m * w.tiles_n * w.splits * w.nbatch;
     const int data_first = pd.kblk_per_split >= pw.kblk_per_split;
     const bool od = gd.out_dtype == DT_F32 || pd.splits > 1;
     const bool ow = gw.out_dtype == DT_F32 || pw.splits > 1;
     hipError_t e;
+    if (gd.orient == OR_FWD) {   // batched (attention): never split, same output type
+        if (od != ow || pd.splits > 1 || pw.splits > 1 || pd.shift) return hipErrorInvalidValue;
+        return launch_pair_fwd_weight(od, pd, d, w, data_first, grid, s);
+    }
     if (od && ow) e = launch_group_tile<true, true>(pd, d, w, data_first, grid, s);
     else if (od) e = launch_group_tile<true, false>(pd, d, w, data_first, grid, s);
     else if (ow) e = launch_group_tile<false, true>(pd, d, w, data_first, grid, s);

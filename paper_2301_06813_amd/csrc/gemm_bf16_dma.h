@@ -916,9 +916,11 @@ void gemm_bf16_reg_kernel(GemmArgs g) {
 // product (both m/n-major). They are independent (each reads only dY and one
 // of X, W), so their work items share the grid; the product whose work
 // items are longer is dispatched first (data_first) so that the short items
-// of the other fill the machine behind them.
+// of the other fill the machine behind them. The two backward products of an
+// attention product are the same pair, batched, or (D_BKMAJ = false) a pair
+// whose first product has an n-major B: dQ = dS K beside dK = dS^T Q.
 template <int BM, int BN, int BKD, int NS, int WGM, int WGN, int KG, int EPI, bool OUTD_F32,
-          bool OUTW_F32, bool SHIFT = false>
+          bool OUTW_F32, bool SHIFT = false, bool D_BKMAJ = true>
 __global__ __launch_bounds__(64 * WGM * WGN * KG,
                              (Occupancy<BM, BN, BKD, NS, WGM * WGN * KG, KG>::VALUE))
 void gemm_bf16_dma_bwd_kernel(ArgsOf<SHIFT> gd, ArgsOf<SHIFT> gw, int data_first) {
@@ -929,7 +931,7 @@ void gemm_bf16_dma_bwd_kernel(ArgsOf<SHIFT> gd, ArgsOf<SHIFT> gw, int data_first
     const bool is_data = data_first ? (b < wd) : (b >= ww);
     if (is_data) {
         const int local = data_first ? b : b - ww;
-        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, true, true, OUTD_F32, SHIFT>(
+        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, true, D_BKMAJ, OUTD_F32, SHIFT>(
             gd, remap_xcd(local, wd), smem);
     } else {
         const int local = data_first ? b - wd : b;

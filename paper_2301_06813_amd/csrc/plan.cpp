@@ -44,21 +44,22 @@ struct PipeClass {
     double step[3], epi;
 };
 const PipeClass kPipe[] = {
-    {64, 64, 1, 2, {0.336, 0.210, 0.210}, 0.86},    {64, 64, 4, 5, {0.385, 0.264, 0.188}, 0.57},
-    {64, 64, 12, 1, {0.203, 0.203, 0.203}, 2.09},   {64, 128, 4, 3, {0.530, 0.323, 0.282}, 1.04},
-    {64, 128, 12, 1, {0.347, 0.347, 0.347}, 2.75},  {128, 64, 4, 3, {0.530, 0.323, 0.282}, 1.04},
-    {128, 64, 12, 1, {0.347, 0.347, 0.347}, 2.75},  {128, 128, 4, 2, {0.667, 0.422, 0.422}, 2.06},
-    {128, 128, 12, 1, {0.505, 0.505, 0.505}, 3.78}, {256, 192, 1, 1, {1.186, 1.186, 1.186}, 4.01},
-    {256, 256, 1, 1, {1.558, 1.558, 1.558}, 4.31},
+    {64, 64, 1, 2, {0.325, 0.203, 0.203}, 0.77},    {64, 64, 4, 5, {0.378, 0.255, 0.184}, 0.48},
+    {64, 64, 12, 1, {0.195, 0.195, 0.195}, 1.99},   {64, 128, 4, 3, {0.521, 0.311, 0.278}, 0.89},
+    {64, 128, 12, 1, {0.338, 0.338, 0.338}, 2.58},  {128, 64, 4, 3, {0.521, 0.311, 0.278}, 0.89},
+    {128, 64, 12, 1, {0.338, 0.338, 0.338}, 2.58},  {128, 128, 4, 2, {0.646, 0.410, 0.410}, 1.89},
+    {128, 128, 12, 1, {0.491, 0.491, 0.491}, 3.51}, {256, 192, 1, 1, {1.145, 1.145, 1.145}, 3.83},
+    {256, 256, 1, 1, {1.487, 1.487, 1.487}, 4.36},
 };
 
 constexpr double kCUs = 256.0;
 constexpr double kFixed = 5.2;         // launch, first loads, last stores (us)
-constexpr double kHbm = 5.6e6;         // bytes per us of a product that streams (mixed)
+constexpr double kHbm = 7.3e6;         // bytes per us, of which the compute units' time
+constexpr double kOverlap = 0.21;      // hides all but this share of the smaller
 constexpr double kReduce = 0.88;       // the split reduction's launch (us), ...
 constexpr double kReduceLoads = 0.32;  // each four slices it reads one after another
 constexpr double kReduceRate = 5.40e6; // and its bytes per us, partials written and read
-constexpr double kKmajor = 0.965;     // step time with both operands k-major
+constexpr double kKmajor = 0.957;     // step time with both operands k-major
 
 thread_local int ov_bm = 0, ov_bn = 0, ov_splits = 1, ov_kernel = 0, ov_occ = 0;
 thread_local int ov_orients = 7;   // orientations the override applies to (bit per Orient)
@@ -202,6 +203,12 @@ double reduce_time(const Gemm &g, int splits) {
 
 double reduce_loads(int splits) { return kReduceLoads * ((splits + 3) / 4); }
 
+// Time t of the compute units beside `bytes` of memory traffic.
+double overlapped(double t, double bytes) {
+    const double h = bytes / kHbm;
+    return std::max(t, h) + kOverlap * std::min(t, h);
+}
+
 // One product: the busiest unit's items in turn (beyond four the units even
 // out), not faster than its bytes, then the split reduction.
 double model_time(const Gemm &g, const PipeClass &c, int splits, int per) {
@@ -209,13 +216,13 @@ double model_time(const Gemm &g, const PipeClass &c, int splits, int per) {
     const double q = i.n / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
     const double r = std::min((double)c.res, std::ceil(q));
     const double t = busy * (i.steps * step_of(c, r) + i.epi);
-    return kFixed + std::max(t, algo_bytes(g) / kHbm) +
+    return kFixed + overlapped(t, algo_bytes(g)) +
            (splits > 1 ? kReduce + reduce_loads(splits) + reduce_time(g, splits) : 0.0);
 }
 
 // Two products sharing one grid: the longer items are dispatched first and
 // the shorter fill in behind them. The whole lasts at least as long as the
-// even share of a unit plus 0.6 of a short item, and as one long item, whose
+// even share of a unit plus half a short item, and as one long item, whose
 // steps wait for the other workgroups of its unit (0.7 of taking turns with all
 // of them to the end: they finish sooner).
 double model_pair(const Gemm &gd, const Gemm &gw, const PipeClass &c, int sd, int pd, int sw,
@@ -229,15 +236,21 @@ double model_pair(const Gemm &gd, const Gemm &gw, const PipeClass &c, int sd, in
     const double c2 = data_first ? cw : cd;
     double t = std::max(c1, c2);
     if (q > 1.0)
-        t = std::max(std::ceil(n1 / kCUs) * c1, (d.n * cd + w.n * cw) / kCUs + 0.6 * c2);
+        t = std::max(std::ceil(n1 / kCUs) * c1, (d.n * cd + w.n * cw) / kCUs + 0.55 * c2);
     const double wait = std::max(c.step[0], r > 1.0 ? 0.7 * r * step : 0.0);
     t = std::max(t, std::max(d.steps * wait + d.epi, w.steps * wait + w.epi));
-    return kFixed + std::max(t, (algo_bytes(gd) + algo_bytes(gw)) / kHbm) +
+    return kFixed + overlapped(t, algo_bytes(gd) + algo_bytes(gw)) +
            (sd > 1 || sw > 1 ? kReduce + reduce_loads(std::max(sd, sw)) : 0.0) +
            reduce_time(gd, sd) + reduce_time(gw, sw);
 }
 
 }  // namespace
+
+static bool pipe_class(int bm, int bn, int code) {
+    for (const PipeClass &c : kPipe)
+        if (c.bm == bm && c.bn == bn && c.code == code) return true;
+    return false;
+}
 
 bool tile_supported(int bm, int bn, bool dma) {
     if (dma) {
@@ -405,6 +418,11 @@ Plan plan_f32(const Gemm &g) {
     return cached_plan(g, g.lda > kMaxLd || g.ldb > kMaxLd);
 }
 
+static double work_items(const Gemm &g, const Plan &p) {
+    return (double)((g.m + p.bm - 1) / p.bm + 1) * (double)((g.n + p.bn - 1) / p.bn + 1) *
+           p.splits * (double)g.nbatch();
+}
+
 // Grouped plan of both products on instance `in` (tile bm x bn) with the
 // given splits; false if it does not fit the workspace.
 static bool grouped_plan(const Gemm &gd, const Gemm &gw, const Instance *in, int bm, int bn,
@@ -418,6 +436,9 @@ static bool grouped_plan(const Gemm &gd, const Gemm &gw, const Instance *in, int
         p.shift = sh;
         split_of(kblocks(g.k), w ? sw : sd, &p.splits, &p.kblk_per_split);
     }
+    // a batched product is never split, and all work items fit a 31-bit index
+    if ((gd.nbatch() > 1 && pd->splits > 1) || (gw.nbatch() > 1 && pw->splits > 1)) return false;
+    if (work_items(gd, *pd) + work_items(gw, *pw) > 2147483647.0) return false;
     return (double)plan_ws_floats(gd, *pd) + (double)plan_ws_floats(gw, *pw) <= ws_budget(gd);
 }
 
@@ -426,26 +447,26 @@ size_t plan_ws_floats(const Gemm &g, const Plan &p) {
 }
 
 static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
-    if (gd.nbatch() > 1 || gw.nbatch() > 1) {   // batched products run one by one
-        *pd = plan_bf16(gd);
-        *pw = plan_bf16(gw);
-        return false;
-    }
     *pd = plan_bf16(gd);
     *pw = plan_bf16(gw);
+    const bool attn = gd.orient == OR_FWD;   // dQ beside dK
     if (ov_bwd_mode == 1) return false;
-    if (ov_bm != 0 && ov_kernel == 2) return false;
+    if (ov_bm != 0 && (ov_kernel == 2 || ((attn || gd.nbatch() > 1) && ov_bwd_mode != 2)))
+        return false;
     if (!dma_eligible(gd) || !dma_eligible(gw)) return false;
+    if (attn && (gd.out_dtype != gw.out_dtype || dma_mode(gd) == 2 || dma_mode(gw) == 2))
+        return false;
     if (ov_bm != 0 && ov_bwd_mode == 2) {
         // tuning: grouped on the override's instance, backward-data splits from
         // the plan override, backward-weight splits from the backward override
         const Instance *in = find_instance(ov_kernel == 0 ? 1 : ov_kernel, ov_bm, ov_bn);
+        if (attn && !pipe_class(ov_bm, ov_bn, in ? in->code : 0)) return false;
         return in && grouped_plan(gd, gw, in, ov_bm, ov_bn, ov_splits, ov_bwd_splits_w, pd, pw);
     }
     if (ov_bm == 0) {
         const int fd = gd.out_dtype == DT_F32, fw = gw.out_dtype == DT_F32;
         for (const TunedBwd &t : kTunedBwd) {
-            if (t.md < 0) break;
+            if (t.md < 0 || gd.nbatch() > 1 || attn) break;
             if (t.md == gd.m && t.nd == gd.n && t.kd == gd.k && t.fd == fd && t.mw == gw.m &&
                 t.nw == gw.n && t.kw == gw.k && t.fw == fw) {
                 const Instance *in = find_instance(t.code, t.bm, t.bn);
@@ -455,8 +476,9 @@ static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw
                 break;
             }
         }
-        // measured plans of both products: they run as measured, one after the other
-        if (tuned_for(gd, dma_mode(gd)) && tuned_for(gw, dma_mode(gw))) return false;
+        // measured plans of both products: they run as measured, one after the
+        // other (batched pairs were measured without a grouped form)
+        if (gd.nbatch() == 1 && tuned_for(gd, dma_mode(gd)) && tuned_for(gw, dma_mode(gw))) return false;
     }
     const bool sh = dma_mode(gd) == 2 || dma_mode(gw) == 2;
     if (ov_bm != 0) {
@@ -484,14 +506,14 @@ static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw
     for (const PipeClass &c : kPipe) {
         const Instance &in = *find_instance(c.code, c.bm, c.bn);
         int last_d = 0;
-        for (int a = 1; a <= 16; ++a) {
+        for (int a = 1; a <= (gd.nbatch() > 1 ? 1 : 16); ++a) {
             int sd, perd;
             split_of(kd, a, &sd, &perd);
             if (sd == last_d) continue;
             last_d = sd;
             if (sd > 1 && perd < 2) continue;
             int last_w = 0;
-            for (int b = 1; b <= 16; ++b) {
+            for (int b = 1; b <= (gw.nbatch() > 1 ? 1 : 16); ++b) {
                 int sw, perw;
                 split_of(kw, b, &sw, &perw);
                 if (sw == last_w) continue;

@@ -561,6 +561,9 @@ int linear_bwd(const sbp_view_t *dY, const L *ldy, const sbp_view_t *X, const L 
 
 namespace sbpa {
 int run_gemm(const sbpi::Gemm &g, hipStream_t s) { return run(g, Ws{}, s); }
+int run_gemm_pair(const sbpi::Gemm &gd, const sbpi::Gemm &gw, hipStream_t s) {
+    return run_pair(gd, gw, Ws{}, s);
+}
 }  // namespace sbpa
 
 extern "C" {
