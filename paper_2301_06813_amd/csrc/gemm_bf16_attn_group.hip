@@ -30,7 +30,7 @@ hipError_t launch_attn_tile(const Plan &p, const sbpk::GemmArgs &d, const sbpk::
 #define SBP_ATTN_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                              \
     if (p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ && (p.ns == 0 || p.ns == NS_) &&             \
         p.kg == KG_ && p.epi == EPI_) {                                                        \
-        snprintf(name, sizeof(name),                                                           \
+        if (profiling()) snprintf(name, sizeof(name),                                                           \
                  "gemm_bf16_dma_bwd_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s, false, "    \
                  "false>",                                                                     \
                  BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf, tf);                          \

@@ -23,7 +23,7 @@ hipError_t launch_group_tile(const Plan &p, const sbpk::GemmArgsShift &ds,
 #define SBP_BWD_SHIFT_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                         \
     if (p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ && (p.ns == 0 || p.ns == NS_) &&             \
         p.kg == KG_ && p.epi == EPI_) {                                                        \
-        snprintf(name, sizeof(name),                                                           \
+        if (profiling()) snprintf(name, sizeof(name),                                                           \
                  "gemm_bf16_dma_bwd_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s, true>",    \
                  BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf[OD], tf[OW]);                 \
         return launch_kernel(                                                                  \
@@ -38,7 +38,7 @@ hipError_t launch_group_tile(const Plan &p, const sbpk::GemmArgsShift &ds,
 #define SBP_BWD_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                           \
     if (p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ && (p.ns == 0 || p.ns == NS_) &&         \
         p.kg == KG_ && p.epi == EPI_) {                                                    \
-        snprintf(name, sizeof(name),                                                       \
+        if (profiling()) snprintf(name, sizeof(name),                                                       \
                  "gemm_bf16_dma_bwd_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s>", BM_,  \
                  BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf[OD], tf[OW]);                   \
         return launch_kernel(                                                              \

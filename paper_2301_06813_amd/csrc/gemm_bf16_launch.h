@@ -103,7 +103,7 @@ static hipError_t launch_tile(const Plan &p, const sbpk::GemmArgsShift &as, int 
 #define SBP_DMA_SHIFT_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                      \
     if (p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ && (p.ns == 0 || p.ns == NS_) &&          \
         p.kg == KG_ && p.epi == EPI_) {                                                     \
-        snprintf(name, sizeof(name),                                                        \
+        if (profiling()) snprintf(name, sizeof(name),                                                        \
                  "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s, %s, true>",  \
                  BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF]);    \
         return launch_kernel(                                                               \
@@ -117,7 +117,7 @@ static hipError_t launch_tile(const Plan &p, const sbpk::GemmArgsShift &as, int 
     }
 #define SBP_TILE(BM_, BN_, WGM_, WGN_, KG_, EPI_)                                            \
     if (!p.dma && p.bm == BM_ && p.bn == BN_) {                                             \
-        snprintf(name, sizeof(name), "gemm_bf16_reg_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s>", \
+        if (profiling()) snprintf(name, sizeof(name), "gemm_bf16_reg_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s>", \
                  BM_, BN_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF]);               \
         return launch_kernel(                                                               \
             sbpk::gemm_bf16_reg_kernel<BM_, BN_, WGM_, WGN_, KG_, EPI_, AK, BK_, OUTF>,     \
@@ -126,7 +126,7 @@ static hipError_t launch_tile(const Plan &p, const sbpk::GemmArgsShift &as, int 
 #define SBP_DMA_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                            \
     if (p.dma && p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ &&                               \
         (p.ns == 0 || p.ns == NS_) && p.kg == KG_ && p.epi == EPI_) {                       \
-        snprintf(name, sizeof(name),                                                        \
+        if (profiling()) snprintf(name, sizeof(name),                                                        \
                  "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s, %s>", BM_,   \
                  BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF]);         \
         return launch_kernel(                                                               \

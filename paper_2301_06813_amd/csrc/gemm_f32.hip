@@ -313,7 +313,7 @@ static hipError_t launch_f32_orient(const Gemm &g, const Plan &p, float *ws, hip
     a.accumulate = g.accumulate;
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n * a.splits));
     if (!p.dma) {
-        snprintf(name, sizeof(name), "gemm_f32_kernel<%s, %s>", tf[AK], tf[BK_]);
+        if (profiling()) snprintf(name, sizeof(name), "gemm_f32_kernel<%s, %s>", tf[AK], tf[BK_]);
         return launch_kernel(sbpk::gemm_f32_kernel<AK, BK_>, name, grid, dim3(256), s, a);
     }
     // 16-byte loads need every row of both operands on 16-byte chunks
@@ -324,7 +324,7 @@ static hipError_t launch_f32_orient(const Gemm &g, const Plan &p, float *ws, hip
     hipError_t e = hipErrorInvalidValue;
 #define SBP_F32_TILE(BM_)                                                                    \
     if (p.bm == BM_) {                                                                       \
-        snprintf(name, sizeof(name), "gemm_f32_mfma_kernel<%d, %d, %s, %s, %d>", BM_, BM_,   \
+        if (profiling()) snprintf(name, sizeof(name), "gemm_f32_mfma_kernel<%d, %d, %s, %s, %d>", BM_, BM_,   \
                  tf[AK], tf[BK_], v4 ? 4 : 1);                                               \
         e = v4 ? launch_kernel(sbpk::gemm_f32_mfma_kernel<BM_, BM_, AK, BK_, 4>, name, grid, \
                                dim3(256), s, a)                                              \

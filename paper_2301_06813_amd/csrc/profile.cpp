@@ -18,6 +18,8 @@ struct Profile {
 thread_local Profile g_prof;
 }  // namespace
 
+bool profiling() { return g_prof.active && g_prof.count < (int)g_prof.slots.size(); }
+
 ProfileSlot *profile_next() {
     Profile &p = g_prof;
     if (!p.active || p.count >= (int)p.slots.size()) return nullptr;

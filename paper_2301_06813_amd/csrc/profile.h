@@ -18,6 +18,10 @@ struct ProfileSlot {
     char name[160];
 };
 
+// Whether this thread's next launch is recorded (launchers only then format
+// the kernel's name).
+bool profiling();
+
 // Next free slot of this thread's profile, or nullptr when not profiling
 // (or when the profile is full).
 ProfileSlot *profile_next();

@@ -126,16 +126,16 @@ def run_L(op: str, L: dict, X, W, dY, out, stream=None, accumulate=False, ws=Non
     to out's fp32 contents (gradient accumulation); ws: the workspace
     argument of the binding (None: its default workspace)."""
     nd = isinstance(L["x"], sbp.sbp_nd_layout_t)
-    fns = {"fwd": sbp.sbp_nd_linear_fwd if nd else sbp.sbp_linear_fwd,
-           "bwd_data": sbp.sbp_nd_linear_bwd_data if nd else sbp.sbp_linear_bwd_data,
-           "bwd_weight": sbp.sbp_nd_linear_bwd_weight if nd else sbp.sbp_linear_bwd_weight}
     o = sbp.view(out, sbp.SBP_ACCUMULATE if accumulate else sbp.SBP_LOCAL)
     if op == "fwd":
-        return fns[op](sbp.view(X), L["x"], sbp.view(W), L["w"], o, stream, ws)
+        fn = sbp.sbp_nd_linear_fwd if nd else sbp.sbp_linear_fwd
+        return fn(sbp.view(X), L["x"], sbp.view(W), L["w"], o, stream, ws)
     if op == "bwd_data":
-        return fns[op](sbp.view(dY), L["dy"], sbp.view(W), L["w"], o, stream, ws)
+        fn = sbp.sbp_nd_linear_bwd_data if nd else sbp.sbp_linear_bwd_data
+        return fn(sbp.view(dY), L["dy"], sbp.view(W), L["w"], o, stream, ws)
     if op == "bwd_weight":
-        return fns[op](sbp.view(X), L["x"], sbp.view(dY), L["dy"], o, stream, ws)
+        fn = sbp.sbp_nd_linear_bwd_weight if nd else sbp.sbp_linear_bwd_weight
+        return fn(sbp.view(X), L["x"], sbp.view(dY), L["dy"], o, stream, ws)
     raise ValueError(op)
 
 

@@ -243,47 +243,71 @@ def _check(code):
 
 
 # ------------------------------------------------------------------- views
+_dtypes = {}   # torch dtype -> sbp_dtype_t, filled on first use
+
+
+def _dtype_of(t):
+    dt = _dtypes.get(t.dtype)
+    if dt is None:
+        import torch
+        _dtypes.update({torch.bfloat16: SBP_BF16, torch.float32: SBP_F32})
+        dt = _dtypes.get(t.dtype)
+        if dt is None:
+            raise TypeError("unsupported dtype %s" % t.dtype)
+    return dt
+
+
 def view(t, scope=SBP_GLOBAL) -> sbp_view_t:
     """sbp_view_t of a 2-D torch tensor whose columns are contiguous."""
-    import torch
-    if t.dim() != 2:
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError("views are 2-D")
-    if t.stride(1) != 1 and t.shape[1] > 1:
+    rows, cols = shape
+    ld, step = t.stride()
+    if step != 1 and cols > 1:
         raise ValueError("views need unit column stride")
-    dt = {torch.bfloat16: SBP_BF16, torch.float32: SBP_F32}.get(t.dtype)
-    if dt is None:
-        raise TypeError("unsupported dtype %s" % t.dtype)
-    ld = max(t.stride(0), t.shape[1], 1)
-    return sbp_view_t(t.data_ptr(), t.shape[0], t.shape[1], ld, dt, scope)
+    return sbp_view_t(t.data_ptr(), rows, cols, max(ld, cols, 1), _dtype_of(t), scope)
 
 
 def view4(t, scope=SBP_GLOBAL) -> sbp_view4_t:
     """sbp_view4_t of a 4-D torch tensor [batch][heads][rows][cols] (any
     strides with unit column stride; e.g. a permuted view into a fused QKV
     activation)."""
-    import torch
-    if t.dim() != 4:
+    shape = t.shape
+    if len(shape) != 4:
         raise ValueError("view4 needs a 4-D tensor")
-    if t.stride(3) != 1 and t.shape[3] > 1:
+    batch, heads, rows, cols = shape
+    sb, sh, ld, step = t.stride()
+    if step != 1 and cols > 1:
         raise ValueError("views need unit column stride")
-    dt = {torch.bfloat16: SBP_BF16, torch.float32: SBP_F32}.get(t.dtype)
-    if dt is None:
-        raise TypeError("unsupported dtype %s" % t.dtype)
-    ld = max(t.stride(2), t.shape[3], 1)
-    return sbp_view4_t(t.data_ptr(), t.shape[0], t.shape[1], t.shape[2], t.shape[3],
-                       t.stride(0), t.stride(1), ld, dt, scope)
+    return sbp_view4_t(t.data_ptr(), batch, heads, rows, cols, sb, sh, max(ld, cols, 1),
+                       _dtype_of(t), scope)
 
 
 def raw_view(ptr, rows, cols, ld, dtype, scope=SBP_GLOBAL) -> sbp_view_t:
     return sbp_view_t(ptr, rows, cols, ld, dtype, scope)
 
 
+_raw_stream = None   # (handle of a device's current stream, current device), once CUDA is up
+
+
 def current_stream():
+    """Handle of torch's current stream on the current device. (Building the
+    torch.cuda.Stream object costs 2.5 us, a quarter of a small call, so after
+    the first call the handle is asked for directly where torch offers it.)"""
+    global _raw_stream
+    if _raw_stream:
+        return _raw_stream[0](_raw_stream[1]())
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.current_stream().cuda_stream   # initialises CUDA
+    raw = (getattr(torch._C, "_cuda_getCurrentRawStream", None),
+           getattr(torch._C, "_cuda_getDevice", None))
+    if all(raw):
+        _raw_stream = raw
+    return s
 
 
-_default_ws = {}
+_default_ws = {}   # (device, stream) -> (tensor, its sbp_workspace_t)
 
 
 def workspace(t) -> sbp_workspace_t:
@@ -291,22 +315,27 @@ def workspace(t) -> sbp_workspace_t:
     return sbp_workspace_t(t.data_ptr(), t.numel() * t.element_size())
 
 
+def _kept_workspace(stream):
+    import torch
+    device = _raw_stream[1]() if _raw_stream else torch.cuda.current_device()
+    key = (device, int(stream or 0))
+    kept = _default_ws.get(key)
+    if kept is None:
+        t = torch.empty(SBP_WORKSPACE_BYTES, dtype=torch.uint8, device="cuda")
+        kept = _default_ws[key] = (t, workspace(t))
+    return kept
+
+
 def default_workspace(stream) -> sbp_workspace_t:
     """This module's workspace for (current device, stream): SBP_WORKSPACE_BYTES
     allocated with torch on first use and kept (calls on one stream run in
     order, so they can share it)."""
-    import torch
-    key = (torch.cuda.current_device(), int(stream or 0))
-    t = _default_ws.get(key)
-    if t is None:
-        t = torch.empty(SBP_WORKSPACE_BYTES, dtype=torch.uint8, device="cuda")
-        _default_ws[key] = t
-    return workspace(t)
+    return workspace(_kept_workspace(stream)[0])
 
 
 def _ws(ws, stream):
     if ws is None:
-        return default_workspace(stream)
+        return _kept_workspace(stream)[1]
     if isinstance(ws, sbp_workspace_t):
         return ws
     return workspace(ws)
@@ -335,9 +364,11 @@ def _compute(fn, a, la, b, lb, out, stream, ws):
     lo = type(la)()
     s = current_stream() if stream is None else stream
     w = _ws(ws, s)
-    _check(getattr(lib(), fn)(ctypes.byref(a), ctypes.byref(la), ctypes.byref(b),
-                              ctypes.byref(lb), ctypes.byref(out), ctypes.byref(lo),
-                              ctypes.byref(w), ctypes.c_void_p(s)))
+    ref = ctypes.byref
+    rc = getattr(_lib or lib(), fn)(ref(a), ref(la), ref(b), ref(lb), ref(out), ref(lo), ref(w),
+                                    ctypes.c_void_p(s))
+    if rc:
+        _check(rc)
     return lo
 
 
@@ -366,10 +397,11 @@ def sbp_linear_bwd(dY: sbp_view_t, ldy: sbp_layout_t, X: sbp_view_t, lx: sbp_lay
     sx, sw = sbp_layout_t(), sbp_layout_t()
     s = current_stream() if stream is None else stream
     w = _ws(ws, s)
-    _check(lib().sbp_linear_bwd(ctypes.byref(dY), ctypes.byref(ldy), ctypes.byref(X),
-                                ctypes.byref(lx), ctypes.byref(W), ctypes.byref(lw),
-                                ctypes.byref(dX), ctypes.byref(sx), ctypes.byref(dW),
-                                ctypes.byref(sw), ctypes.byref(w), ctypes.c_void_p(s)))
+    ref = ctypes.byref
+    rc = (_lib or lib()).sbp_linear_bwd(ref(dY), ref(ldy), ref(X), ref(lx), ref(W), ref(lw), ref(dX),
+                                   ref(sx), ref(dW), ref(sw), ref(w), ctypes.c_void_p(s))
+    if rc:
+        _check(rc)
     return sx, sw
 
 
@@ -435,10 +467,11 @@ def sbp_nd_linear_bwd(dY, ldy, X, lx, W, lw, dX, dW, stream=None, ws=None):
     sx, sw = sbp_nd_layout_t(), sbp_nd_layout_t()
     s = current_stream() if stream is None else stream
     w = _ws(ws, s)
-    _check(lib().sbp_nd_linear_bwd(ctypes.byref(dY), ctypes.byref(ldy), ctypes.byref(X),
-                                   ctypes.byref(lx), ctypes.byref(W), ctypes.byref(lw),
-                                   ctypes.byref(dX), ctypes.byref(sx), ctypes.byref(dW),
-                                   ctypes.byref(sw), ctypes.byref(w), ctypes.c_void_p(s)))
+    ref = ctypes.byref
+    rc = (_lib or lib()).sbp_nd_linear_bwd(ref(dY), ref(ldy), ref(X), ref(lx), ref(W), ref(lw), ref(dX),
+                                      ref(sx), ref(dW), ref(sw), ref(w), ctypes.c_void_p(s))
+    if rc:
+        _check(rc)
     return sx, sw
 
 
