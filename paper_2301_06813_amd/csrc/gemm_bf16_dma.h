@@ -402,6 +402,45 @@ __device__ __forceinline__ void store_staged(const float *tile, void *C, int64_t
     constexpr int CPR = BN / EPC;                // chunks per tile row
     constexpr int ITER = BM * CPR / NT_;
     static_assert((BM * CPR) % NT_ == 0, "tile not divisible among threads");
+    if constexpr (ACC) {
+        // the old contents of U chunks are loaded before any is stored, so that
+        // a thread waits for one memory latency per U chunks
+        constexpr int U = ITER < 4 ? ITER : 4;
+        float *const base = reinterpret_cast<float *>(C);
+        for (int it = 0; it < ITER; it += U) {
+            f32x4 v[U];
+#pragma unroll
+            for (int ph = 0; ph < 2; ++ph)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = (it + u) * NT_ + tid;
+                    const int r = q / CPR, c = (q % CPR) * EPC;
+                    const int row = m0 + r, col = n0 + c;
+                    if ((unsigned)row >= (unsigned)m || col >= n || col + EPC <= 0) continue;
+                    float *dst = base + (int64_t)row * ldc + col;
+                    const bool whole = vec && col >= 0 && col + 4 <= n;
+                    if (ph == 0) {
+                        if (whole) {
+                            v[u] = *reinterpret_cast<const f32x4_any *>(dst);
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                v[u][e] = (unsigned)(col + e) < (unsigned)n ? dst[e] : 0.f;
+                        }
+                    } else {
+                        v[u] += *reinterpret_cast<const f32x4 *>(tile + r * LD + c);
+                        if (whole) {
+                            *reinterpret_cast<f32x4_any *>(dst) = v[u];
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if ((unsigned)(col + e) < (unsigned)n) dst[e] = v[u][e];
+                        }
+                    }
+                }
+        }
+        return;
+    }
 #pragma unroll 4
     for (int it = 0; it < ITER; ++it) {
         const int q = it * NT_ + tid;
@@ -412,13 +451,10 @@ __device__ __forceinline__ void store_staged(const float *tile, void *C, int64_t
             continue;
         const float *src = tile + r * LD + c;
         if constexpr (F32) {
-            f32x4 v = *reinterpret_cast<const f32x4 *>(src);
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(src);
             float *dst = reinterpret_cast<float *>(C) + (int64_t)row * ldc + col;
             if (vec && (!SHIFT || col >= 0) && col + 4 <= n) {
-                if constexpr (ACC) {
-                    v += *reinterpret_cast<const f32x4_any *>(dst);
-                    *reinterpret_cast<f32x4_any *>(dst) = v;
-                } else if constexpr (PART) {
+                if constexpr (PART) {
                     st_part(part_rsrc(C), (int64_t)row * ldc + col, v);
                 } else {
                     __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any *>(dst));
@@ -427,8 +463,7 @@ __device__ __forceinline__ void store_staged(const float *tile, void *C, int64_t
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (SHIFT ? (unsigned)(col + e) < (unsigned)n : col + e < n) {
-                        if constexpr (ACC) dst[e] = dst[e] + v[e];
-                        else if constexpr (PART) st_part(part_rsrc(C), (int64_t)row * ldc + col + e, v[e]);
+                        if constexpr (PART) st_part(part_rsrc(C), (int64_t)row * ldc + col + e, v[e]);
                         else st_nt(dst + e, v[e]);
                     }
             }
@@ -715,6 +750,19 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                 if (!inb(row, g.m)) continue;
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
+                    // accumulation: all four old quads before any is stored
+                    f32x4 old[4];
+                    if constexpr (ACC) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int col = on0 + wn * WN + j * 32 + 8 * q + 4 * (lane >> 5);
+                            const float *src =
+                                reinterpret_cast<const float *>(out) + (int64_t)row * ldo + col;
+                            old[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                            if (vec && (!SHIFT || col >= 0) && col + 4 <= g.n)
+                                old[q] = *reinterpret_cast<const f32x4 *>(src);
+                        }
+                    }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int col = on0 + wn * WN + j * 32 + 8 * q + 4 * (lane >> 5);
@@ -725,8 +773,7 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                                 f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1],
                                            acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
                                 if constexpr (ACC) {
-                                    v += *reinterpret_cast<const f32x4 *>(dst);
-                                    *reinterpret_cast<f32x4 *>(dst) = v;
+                                    *reinterpret_cast<f32x4 *>(dst) = old[q] + v;
                                 } else if constexpr (PART) {
                                     st_part(part_rsrc(out), (int64_t)row * ldo + col, v);
                                 } else {
@@ -836,13 +883,25 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                 const int col = on0 + wn * WN + j * 32 + (lane & 31);
                 const int rbase = om0 + wm * WM + i * 32 + 4 * (lane >> 5);
                 if (inb(col, g.n)) {
+                    // accumulation: all 16 old values before any is stored, so that
+                    // a lane waits for one memory latency per block, not 16
+                    float old[16];
+                    if constexpr (F32 && ACC) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int row = rbase + 8 * (r >> 2) + (r & 3);
+                            old[r] = inb(row, g.m) ? reinterpret_cast<const float *>(
+                                                         out)[(int64_t)row * ldo + col]
+                                                   : 0.f;
+                        }
+                    }
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int row = rbase + 8 * (r >> 2) + (r & 3);
                         if (inb(row, g.m)) {
                             if constexpr (F32 && ACC) {
-                                float *d = reinterpret_cast<float *>(out) + (int64_t)row * ldo + col;
-                                *d = *d + acc[i][j][r];
+                                reinterpret_cast<float *>(out)[(int64_t)row * ldo + col] =
+                                    old[r] + acc[i][j][r];
                             } else if constexpr (F32 && PART)
                                 st_part(part_rsrc(out), (int64_t)row * ldo + col, acc[i][j][r]);
                             else if constexpr (F32)

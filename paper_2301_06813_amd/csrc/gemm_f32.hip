@@ -191,14 +191,27 @@ __global__ __launch_bounds__(256, BM == 64 ? 4 : 2) void gemm_f32_mfma_kernel(F3
             const int col = n0 + wn * WN + j * 32 + (lane & 31);
             const int rbase = m0 + wm * WM + i * 32 + 4 * (lane >> 5);
             if (col >= g.n) continue;
+            if (g.accumulate && !partial) {
+                // all old values before any is stored: one memory latency
+                float old[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = rbase + 8 * (r >> 2) + (r & 3);
+                    old[r] = row < g.m ? out[(int64_t)row * ldo + col] : 0.f;
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = rbase + 8 * (r >> 2) + (r & 3);
+                    if (row < g.m) out[(int64_t)row * ldo + col] = old[r] + acc[i][j][r];
+                }
+                continue;
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = rbase + 8 * (r >> 2) + (r & 3);
                 if (row >= g.m) continue;
-                float *c = out + (int64_t)row * ldo + col;
                 if (partial) st_part(pr, (int64_t)row * ldo + col, acc[i][j][r]);
-                else if (g.accumulate) *c = *c + acc[i][j][r];
-                else st_nt(c, acc[i][j][r]);
+                else st_nt(out + (int64_t)row * ldo + col, acc[i][j][r]);
             }
         }
 }

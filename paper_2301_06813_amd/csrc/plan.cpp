@@ -59,6 +59,7 @@ constexpr double kOverlap = 0.21;      // hides all but this share of the smalle
 constexpr double kReduce = 0.88;       // the split reduction's launch (us), ...
 constexpr double kReduceLoads = 0.32;  // each four slices it reads one after another
 constexpr double kReduceRate = 5.40e6; // and its bytes per us, partials written and read
+constexpr double kAccumulate = 2.5;    // stores that first load the old contents
 constexpr double kKmajor = 0.957;     // step time with both operands k-major
 
 thread_local int ov_bm = 0, ov_bn = 0, ov_splits = 1, ov_kernel = 0, ov_occ = 0;
@@ -180,8 +181,8 @@ bool fits_ws(const Gemm &g, int splits) {
 double out_elem(const Gemm &g) { return g.out_dtype == DT_F32 ? 4.0 : 2.0; }
 
 double algo_bytes(const Gemm &g) {
-    return (2.0 * ((double)g.m * g.k + (double)g.k * g.n) + out_elem(g) * g.m * g.n) *
-           (double)g.nbatch();
+    const double out = out_elem(g) * (g.accumulate ? 2.0 : 1.0);
+    return (2.0 * ((double)g.m * g.k + (double)g.k * g.n) + out * g.m * g.n) * (double)g.nbatch();
 }
 
 double step_of(const PipeClass &c, double r) { return c.step[r > 2.0 ? 2 : r > 1.0 ? 1 : 0]; }
@@ -195,7 +196,7 @@ Items items_of(const Gemm &g, const PipeClass &c, int splits, int per) {
     const double tiles = (double)((g.m + c.bm - 1) / c.bm) * (double)((g.n + c.bn - 1) / c.bn);
     return {tiles * splits * (double)g.nbatch(),
             per * (g.orient == OR_BWD_DATA ? kKmajor : 1.0),
-            c.epi * (splits > 1 ? 1.0 : out_elem(g) / 4.0)};
+            c.epi * (splits > 1 ? 1.0 : g.accumulate ? kAccumulate : out_elem(g) / 4.0)};
 }
 double reduce_time(const Gemm &g, int splits) {
     return splits > 1 ? (4.0 * splits + out_elem(g)) * g.m * g.n / kReduceRate : 0.0;
@@ -377,7 +378,7 @@ struct KeyHash {
     }
 };
 Key key_of(const Gemm &g, int mode) {
-    return Key{{g.orient, g.in_dtype, g.out_dtype, g.m, g.n, g.k, mode,
+    return Key{{g.orient, g.in_dtype, g.out_dtype + 2 * (g.accumulate ? 1 : 0), g.m, g.n, g.k, mode,
                 ov_bm * 1000 + ov_bn, ((ov_splits * 100 + ov_kernel) * 100 + ov_occ) * 8 + ov_orients,
                 g.nbatch(), (int64_t)std::min(g.ws_floats, WS_FLOATS_PREFERRED)}};
 }
