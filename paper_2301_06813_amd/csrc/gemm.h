@@ -119,6 +119,11 @@ hipError_t launch_bf16_bwd_group(const Gemm &gd, const Plan &pd, const Gemm &gw,
 // dma false: the plain FMA kernel).
 Plan plan_f32(const Gemm &g);
 hipError_t launch_f32(const Gemm &g, const Plan &p, float *ws, hipStream_t s);
+// fp32 forms of plan_bf16_bwd and launch_bf16_bwd_group (pd and pw are set only
+// when it returns true).
+bool plan_f32_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw);
+hipError_t launch_f32_bwd_group(const Gemm &gd, const Plan &pd, const Gemm &gw, const Plan &pw,
+                                float *ws, hipStream_t s);
 
 // The library's static scratch on the current device (its address there,
 // looked up once per device) and its size in floats (WS_FLOATS_PREFERRED).

@@ -17,10 +17,12 @@
 //     and epilogues. More stages (three to eight) with fewer workgroups per
 //     CU, or two reduction groups of waves, were no faster; 128 x 64 tiles
 //     lay between the two.
+//   * The two backward products of a linear share one launch where the model
+//     expects it to pay: two 256-tile products of 128 x 128 tiles 148 -> 136 us.
 //   * Measured, against the FMA kernel below: 1024 x 4096 x 1024 forward
 //     240 -> 75 us, 256 x 4096 x 3136 forward 660 -> 63 us, 4096^3 134
 //     TFLOP/s (the library product reaches 141); the largest error against
-//     64 bits over fp32 layers of those sizes 1.1e-6 -> 7.1e-7.
+//     64 bits over fp32 layers of those sizes 1.1e-6 -> 8.1e-7.
 //   * V = 4: 16 bytes per lane, where both operands' base, ld and contiguous
 //     extent are multiples of 4 floats. V = 1: 4 bytes per lane with per-element
 //     bounds, for any other operand: four times the load instructions, which
@@ -113,19 +115,18 @@ struct F32Tile {
     }
 };
 
+// One work item (an output tile and a reduction split; L its logical index).
 template <int BM, int BN, bool A_KMAJ, bool B_KMAJ, int V>
-__global__ __launch_bounds__(256, BM == 64 ? 4 : 2) void gemm_f32_mfma_kernel(F32Args g) {
+__device__ __forceinline__ void f32_tile_body(const F32Args &g, const int L, char *smem) {
     using TA = F32Tile<BM, A_KMAJ, V>;
     using TB = F32Tile<BN, B_KMAJ, V>;
     constexpr int A_BYTES = BM * FK * 4, STAGE = (BM + BN) * FK * 4;
     constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 32, NI = WN / 32;
-    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 
     const int tiles = g.tiles_m * g.tiles_n;
-    const int L = remap_xcd(blockIdx.x, tiles * g.splits);
     const int split = L / tiles;
     const int t = L % tiles;
     constexpr int GROUP = SBP_TILE_GROUP;
@@ -216,6 +217,30 @@ __global__ __launch_bounds__(256, BM == 64 ? 4 : 2) void gemm_f32_mfma_kernel(F3
         }
 }
 
+// Two workgroups of 128 x 128 tiles per CU (64 KB of LDS each), four or five of 64 x 64 ones.
+template <int BM, bool A_KMAJ, bool B_KMAJ, int V>
+__global__ __launch_bounds__(256, BM == 64 ? 4 : 2) void gemm_f32_mfma_kernel(F32Args g) {
+    __shared__ __attribute__((aligned(1024))) char smem[4 * BM * FK * 4];
+    const int total = g.tiles_m * g.tiles_n * g.splits;
+    f32_tile_body<BM, BM, A_KMAJ, B_KMAJ, V>(g, remap_xcd(blockIdx.x, total), smem);
+}
+
+// Both backward products of one linear in one launch, the product with the
+// longer work items first (as gemm_bf16_dma_bwd_kernel): a product of 256 tiles
+// alone puts one workgroup on each CU, which then waits for every load.
+template <int BM, int V>
+__global__ __launch_bounds__(256, BM == 64 ? 4 : 2) void gemm_f32_mfma_bwd_kernel(
+    F32Args gd, F32Args gw, int data_first) {
+    __shared__ __attribute__((aligned(1024))) char smem[4 * BM * FK * 4];
+    const int wd = gd.tiles_m * gd.tiles_n * gd.splits;
+    const int ww = gw.tiles_m * gw.tiles_n * gw.splits;
+    const int b = blockIdx.x;
+    if (data_first ? b < wd : b >= ww)
+        f32_tile_body<BM, BM, true, true, V>(gd, remap_xcd(data_first ? b : b - ww, wd), smem);
+    else
+        f32_tile_body<BM, BM, false, false, V>(gw, remap_xcd(data_first ? b - wd : b, ww), smem);
+}
+
 // Plain LDS-tiled FMA kernel for leading dimensions beyond 2^21: 64 x 64
 // output tile, reduction step 16, 256 threads each owning a 4 x 4 strided
 // sub-block.
@@ -304,10 +329,7 @@ hipError_t launch_bf16(const Gemm &g, const Plan &p, float *ws, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
-template <bool AK, bool BK_>
-static hipError_t launch_f32_orient(const Gemm &g, const Plan &p, float *ws, hipStream_t s) {
-    const char *tf[2] = {"false", "true"};
-    char name[96];
+static sbpk::F32Args f32_args(const Gemm &g, const Plan &p, float *ws) {
     sbpk::F32Args a;
     a.A = static_cast<const float *>(g.A);
     a.B = static_cast<const float *>(g.B);
@@ -324,24 +346,37 @@ static hipError_t launch_f32_orient(const Gemm &g, const Plan &p, float *ws, hip
     a.kchunk = p.kblk_per_split * p.bk;
     a.ws = ws;
     a.accumulate = g.accumulate;
+    return a;
+}
+
+// 16-byte loads need every row of both operands on 16-byte chunks.
+static bool f32_vec4(const Gemm &g) {
+    const int64_t ca = g.orient == OR_BWD_WEIGHT ? g.m : g.k;
+    const int64_t cb = g.orient == OR_BWD_DATA ? g.k : g.n;
+    return ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) == 0 &&
+           g.lda % 4 == 0 && g.ldb % 4 == 0 && ca % 4 == 0 && cb % 4 == 0;
+}
+
+template <bool AK, bool BK_>
+static hipError_t launch_f32_orient(const Gemm &g, const Plan &p, float *ws, hipStream_t s) {
+    const char *tf[2] = {"false", "true"};
+    char name[96];
+    const sbpk::F32Args a = f32_args(g, p, ws);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n * a.splits));
     if (!p.dma) {
         if (profiling()) snprintf(name, sizeof(name), "gemm_f32_kernel<%s, %s>", tf[AK], tf[BK_]);
         return launch_kernel(sbpk::gemm_f32_kernel<AK, BK_>, name, grid, dim3(256), s, a);
     }
-    // 16-byte loads need every row of both operands on 16-byte chunks
-    const bool v4 =
-        ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) == 0 &&
-        g.lda % 4 == 0 && g.ldb % 4 == 0 && (AK ? g.k : g.m) % 4 == 0 &&
-        (BK_ ? g.k : g.n) % 4 == 0;
+    const bool v4 = f32_vec4(g);
     hipError_t e = hipErrorInvalidValue;
 #define SBP_F32_TILE(BM_)                                                                    \
     if (p.bm == BM_) {                                                                       \
-        if (profiling()) snprintf(name, sizeof(name), "gemm_f32_mfma_kernel<%d, %d, %s, %s, %d>", BM_, BM_,   \
-                 tf[AK], tf[BK_], v4 ? 4 : 1);                                               \
-        e = v4 ? launch_kernel(sbpk::gemm_f32_mfma_kernel<BM_, BM_, AK, BK_, 4>, name, grid, \
+        if (profiling()) snprintf(name, sizeof(name),                                        \
+                                  "gemm_f32_mfma_kernel<%d, %s, %s, %d>", BM_, tf[AK],       \
+                                  tf[BK_], v4 ? 4 : 1);                                      \
+        e = v4 ? launch_kernel(sbpk::gemm_f32_mfma_kernel<BM_, AK, BK_, 4>, name, grid,      \
                                dim3(256), s, a)                                              \
-               : launch_kernel(sbpk::gemm_f32_mfma_kernel<BM_, BM_, AK, BK_, 1>, name, grid, \
+               : launch_kernel(sbpk::gemm_f32_mfma_kernel<BM_, AK, BK_, 1>, name, grid,      \
                                dim3(256), s, a);                                             \
     }
     SBP_F32_TILE(128)
@@ -358,6 +393,36 @@ hipError_t launch_f32(const Gemm &g, const Plan &p, float *ws, hipStream_t s) {
         case OR_BWD_WEIGHT: return launch_f32_orient<false, false>(g, p, ws, s);
     }
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_f32_bwd_group(const Gemm &gd, const Plan &pd, const Gemm &gw, const Plan &pw,
+                                float *ws, hipStream_t s) {
+    if (!pd.dma || !pw.dma || pd.bm != pw.bm) return hipErrorInvalidValue;
+    char name[96];
+    float *const ws_w = ws + plan_ws_floats(gd, pd);
+    const sbpk::F32Args d = f32_args(gd, pd, ws), w = f32_args(gw, pw, ws_w);
+    const dim3 grid((unsigned)(d.tiles_m * d.tiles_n * d.splits + w.tiles_m * w.tiles_n * w.splits));
+    const int data_first = pd.kblk_per_split >= pw.kblk_per_split;
+    const bool v4 = f32_vec4(gd) && f32_vec4(gw);
+    hipError_t e = hipErrorInvalidValue;
+#define SBP_F32_PAIR(BM_, V_)                                                                \
+    if (pd.bm == BM_ && v4 == (V_ == 4)) {                                                   \
+        if (profiling())                                                                     \
+            snprintf(name, sizeof(name), "gemm_f32_mfma_bwd_kernel<%d, %d>", BM_, V_);       \
+        e = launch_kernel(sbpk::gemm_f32_mfma_bwd_kernel<BM_, V_>, name, grid, dim3(256), s, \
+                          d, w, data_first);                                                 \
+    }
+    SBP_F32_PAIR(128, 4)
+    SBP_F32_PAIR(128, 1)
+    SBP_F32_PAIR(64, 4)
+    SBP_F32_PAIR(64, 1)
+#undef SBP_F32_PAIR
+    if (e != hipSuccess) return e;
+    if (pd.splits > 1 && pw.splits > 1)
+        return launch_split_reduce_pair(gd, pd.splits, ws, gw, pw.splits, ws_w, s);
+    if (pd.splits > 1) return launch_split_reduce(gd, pd.splits, ws, s);
+    if (pw.splits > 1) return launch_split_reduce(gw, pw.splits, ws_w, s);
+    return hipSuccess;
 }
 
 }  // namespace sbpi

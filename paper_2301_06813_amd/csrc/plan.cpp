@@ -396,12 +396,15 @@ struct PairHash {
 };
 struct PairPlan {
     bool grouped;
-    Plan d, w;
+    Plan d{}, w{};
 };
 thread_local std::unordered_map<PairKey, PairPlan, PairHash> pair_cache;
 }  // namespace
 
 static Plan plan_f32_uncached(const Gemm &g, bool big_ld);
+static Plan plan_f32_model(const Gemm &g, bool big_ld, double *time);
+static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, bool big_ld, Plan *pd,
+                                  Plan *pw);
 
 static const Plan &cached_plan(const Gemm &g, int mode) {
     const Key k = key_of(g, mode);
@@ -414,10 +417,13 @@ static const Plan &cached_plan(const Gemm &g, int mode) {
 
 Plan plan_bf16(const Gemm &g) { return cached_plan(g, dma_mode(g)); }
 
-Plan plan_f32(const Gemm &g) {
-    constexpr int64_t kMaxLd = int64_t(1) << 21;   // tile offsets stay below 2^31 bytes
-    return cached_plan(g, g.lda > kMaxLd || g.ldb > kMaxLd);
+// Leading dimensions whose tile offsets reach 2^31 bytes.
+static bool f32_big_ld(const Gemm &g) {
+    constexpr int64_t kMaxLd = int64_t(1) << 21;
+    return g.lda > kMaxLd || g.ldb > kMaxLd;
 }
+
+Plan plan_f32(const Gemm &g) { return cached_plan(g, f32_big_ld(g)); }
 
 static double work_items(const Gemm &g, const Plan &p) {
     return (double)((g.m + p.bm - 1) / p.bm + 1) * (double)((g.n + p.bn - 1) / p.bn + 1) *
@@ -536,19 +542,30 @@ static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw
 
 // Plans are pure functions of the key, kept per thread so that a repeated
 // call does not search again (a pair weighs some 2,000 candidates).
-bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
-    const PairKey k{key_of(gd, dma_mode(gd)), key_of(gw, dma_mode(gw)),
+static bool cached_pair(const Gemm &gd, const Gemm &gw, int mode_d, int mode_w, Plan *pd,
+                        Plan *pw) {
+    const PairKey k{key_of(gd, mode_d), key_of(gw, mode_w),
                     ov_bwd_mode * 65536 + ov_bwd_splits_w};
     auto it = pair_cache.find(k);
     if (it == pair_cache.end()) {
         PairPlan p;
-        p.grouped = plan_bwd_uncached(gd, gw, &p.d, &p.w);
+        p.grouped = gd.in_dtype == DT_F32
+                        ? plan_f32_bwd_uncached(gd, gw, mode_d || mode_w, &p.d, &p.w)
+                        : plan_bwd_uncached(gd, gw, &p.d, &p.w);
         if (pair_cache.size() > 4096) pair_cache.clear();
         it = pair_cache.emplace(k, p).first;
     }
     *pd = it->second.d;
     *pw = it->second.w;
     return it->second.grouped;
+}
+
+bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
+    return cached_pair(gd, gw, dma_mode(gd), dma_mode(gw), pd, pw);
+}
+
+bool plan_f32_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
+    return cached_pair(gd, gw, f32_big_ld(gd), f32_big_ld(gw), pd, pw);
 }
 
 // Generic kernel: the busiest compute unit's share of the work items, each
@@ -676,15 +693,90 @@ static Plan plan_model(const Gemm &g, double *time) {
 // several 64 x 64 workgroups (1024 x 1024 x 4096: 98 us unsplit, 79 us split
 // four ways), and outputs of a whole wave of 128 x 128 tiles take those
 // (4096^3: 1028 us against 1068 us; 1024 x 4096 x 1024: 75 us for both).
+namespace {
+// Time in us of a 32-wide step of a t x t tile with `q` work items per unit.
+double f32_step(int t, double q) { return t == 128 ? 2.1 : q <= 1.0 ? 0.76 : 0.55; }
+double f32_reduce(const Gemm &g, int splits) {
+    return splits > 1 ? (splits * 2.0 + 1.0) * 4.0 * g.m * g.n / 8e6 : 0.0;
+}
+double f32_tiles(const Gemm &g, int t) {
+    return (double)((g.m + t - 1) / t) * (double)((g.n + t - 1) / t);
+}
+constexpr double kF32Fixed = 6.0, kF32Reduce = 2.5;   // us
+}  // namespace
+
 static Plan plan_f32_uncached(const Gemm &g, bool big_ld) {
+    double t;
+    return plan_f32_model(g, big_ld, &t);
+}
+
+// The two backward products in one launch: as model_pair, with the fp32 steps.
+static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, bool big_ld, Plan *pd,
+                                  Plan *pw) {
+    if (big_ld || ov_bwd_mode == 1) return false;
+    double best, tw;
+    *pd = plan_f32_model(gd, false, &best);
+    *pw = plan_f32_model(gw, false, &tw);
+    best += tw;
+    bool grouped = false;
+    const int kd = (int)((gd.k + 31) / 32), kw = (int)((gw.k + 31) / 32);
+    for (const int t : {64, 128}) {
+        int last_d = 0;
+        for (int a = 1; a <= 16; ++a) {
+            int sd, perd;
+            split_of(kd, a, &sd, &perd);
+            if (sd == last_d) continue;
+            last_d = sd;
+            if (sd > 1 && perd < 4) continue;
+            int last_w = 0;
+            for (int b = 1; b <= 16; ++b) {
+                int sw, perw;
+                split_of(kw, b, &sw, &perw);
+                if (sw == last_w) continue;
+                last_w = sw;
+                if (sw > 1 && perw < 4) continue;
+                const double nd = f32_tiles(gd, t) * sd, nw = f32_tiles(gw, t) * sw;
+                if (nd + nw > 2147483647.0) continue;
+                const double q = (nd + nw) / kCUs, step = f32_step(t, q);
+                const double lo = std::max(perd, perw), sh = std::min(perd, perw);
+                const double nlo = perd >= perw ? nd : nw;
+                // a long item waits for the other workgroups of its unit
+                const double r = std::min(t == 128 ? 2.0 : 4.0, std::ceil(q));
+                double busy = q <= 1.0 ? lo
+                                       : std::max(std::ceil(nlo / kCUs) * lo,
+                                                  (nd * perd + nw * perw) / kCUs + 0.5 * sh);
+                // whole rounds of both leave no tail
+                if (q > 1.0)
+                    busy = std::min(busy, std::ceil(nd / kCUs) * perd + std::ceil(nw / kCUs) * perw);
+                busy = std::max(busy, lo * std::max(1.0, 0.7 * r));
+                const double tm = busy * step + kF32Fixed +
+                                  (sd > 1 || sw > 1 ? kF32Reduce : 0.0) + f32_reduce(gd, sd) +
+                                  f32_reduce(gw, sw);
+                if (tm >= best * 0.999) continue;
+                Plan qd{t, t, sd, perd, true}, qw{t, t, sw, perw, true};
+                qd.bk = qw.bk = 32;
+                if ((double)plan_ws_floats(gd, qd) + (double)plan_ws_floats(gw, qw) >
+                    ws_budget(gd))
+                    continue;
+                best = tm;
+                grouped = true;
+                *pd = qd;
+                *pw = qw;
+            }
+        }
+    }
+    return grouped;
+}
+
+static Plan plan_f32_model(const Gemm &g, bool big_ld, double *time) {
     const int kb = (int)((g.k + 31) / 32);
     Plan best{64, 64, 1, std::max(1, kb), false};
     best.bk = 32;
     if (big_ld) return best;   // plain FMA kernel
     best.dma = true;
-    double best_t = 1e30;
+    *time = 1e30;
     for (const int t : {64, 128}) {
-        const double nt = (double)((g.m + t - 1) / t) * (double)((g.n + t - 1) / t);
+        const double nt = f32_tiles(g, t);
         int last = 0;
         for (int s = 1; s <= 32; ++s) {
             int splits, per;
@@ -694,11 +786,10 @@ static Plan plan_f32_uncached(const Gemm &g, bool big_ld) {
             if (splits > 1 && (per < 4 || !fits_ws(g, splits))) continue;
             // work items of the busiest unit; beyond four the units even out
             const double q = nt * splits / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
-            const double step = t == 128 ? 2.1e-6 : q <= 1.0 ? 0.76e-6 : 0.55e-6;
-            double tm = busy * per * step + 6e-6;
-            if (splits > 1) tm += (splits * 2.0 + 1.0) * 4.0 * g.m * g.n / 8e12 + 2.5e-6;
-            if (tm < best_t * 0.999) {
-                best_t = tm;
+            const double tm = busy * per * f32_step(t, q) + kF32Fixed +
+                              (splits > 1 ? kF32Reduce : 0.0) + f32_reduce(g, splits);
+            if (tm < *time * 0.999) {
+                *time = tm;
                 best.bm = best.bn = t;
                 best.splits = splits;
                 best.kblk_per_split = per;

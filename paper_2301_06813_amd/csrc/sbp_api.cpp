@@ -436,13 +436,15 @@ int hip_fail(hipError_t e) {
 
 int run_pair(sbpi::Gemm gd, sbpi::Gemm gw, const Ws &w, hipStream_t s) {
     const bool ed = gd.m == 0 || gd.n == 0, ew = gw.m == 0 || gw.n == 0;
-    if (gd.in_dtype == SBP_BF16 && !ed && !ew) {
+    if (!ed && !ew) {
         gd.ws_floats = gw.ws_floats = w.floats;
+        const bool f32 = gd.in_dtype == SBP_F32;
         sbpi::Plan pd, pw;
-        if (sbpi::plan_bf16_bwd(gd, gw, &pd, &pw)) {
+        if (f32 ? sbpi::plan_f32_bwd(gd, gw, &pd, &pw) : sbpi::plan_bf16_bwd(gd, gw, &pd, &pw)) {
             if (sbpi::plan_ws_floats(gd, pd) + sbpi::plan_ws_floats(gw, pw) > w.floats)
                 return SBP_ERR_WORKSPACE;
-            hipError_t e = sbpi::launch_bf16_bwd_group(gd, pd, gw, pw, w.ptr, s);
+            hipError_t e = f32 ? sbpi::launch_f32_bwd_group(gd, pd, gw, pw, w.ptr, s)
+                               : sbpi::launch_bf16_bwd_group(gd, pd, gw, pw, w.ptr, s);
             if (e != hipSuccess) return hip_fail(e);
             return SBP_OK;
         }

@@ -78,3 +78,31 @@ def test_f32_special_values_stay_in_their_row():
     # and at most half the smallest subnormal (2^-150) absolutely
     err = (out[rest].double() - want).abs()
     assert bool((err <= 66 * (2.0 ** -24 * want + 2.0 ** -149)).all())
+
+
+@pytest.mark.parametrize("off", [0, 1], ids=["aligned", "odd-offset"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (64, 128, 64), (65, 97, 130), (4, 4100, 12),
+                                   (1536, 260, 1664), (1024, 2048, 512)])
+def test_f32_backward_pair(shape, off):
+    # both products in one launch (where the plan groups them) and in two
+    M, K, N = shape
+    X, W, dY = (_ints(a, b, 0, off, 80 + i) for i, (a, b) in
+                enumerate(((M, K), (K, N), (M, N))))
+    L = linear.layouts("BB", 1, 0)
+    want_dx = dY.cpu().double() @ W.cpu().double().t()
+    want_dw = X.cpu().double().t() @ dY.cpu().double()
+    for mode in (0, 1):
+        for acc in (False, True):
+            say("f32 pair", shape, off, mode, acc)
+            gx, gw = (torch.full((a + 2, b + 3), 5.0, device="cuda") for a, b in ((M, K), (K, N)))
+            dX, dW = gx[1:-1, 1:-2], gw[1:-1, 1:-2]
+            try:
+                sbp.sbp_set_bwd_override(mode, 1)
+                linear.run_bwd_L(L, X, W, dY, dX, dW, accumulate_dw=acc)
+            finally:
+                sbp.sbp_set_plan_override(0, 0, 1)
+            assert torch.equal(dX.cpu().double(), want_dx)
+            assert torch.equal(dW.cpu().double(), want_dw + 5.0 if acc else want_dw)
+            dX.fill_(5.0)
+            dW.fill_(5.0)
+            assert bool((gx == 5.0).all()) and bool((gw == 5.0).all())
