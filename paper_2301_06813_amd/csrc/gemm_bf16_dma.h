@@ -883,26 +883,36 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                 const int col = on0 + wn * WN + j * 32 + (lane & 31);
                 const int rbase = om0 + wm * WM + i * 32 + 4 * (lane >> 5);
                 if (inb(col, g.n)) {
-                    // accumulation: all 16 old values before any is stored, so that
-                    // a lane waits for one memory latency per block, not 16
-                    float old[16];
                     if constexpr (F32 && ACC) {
+                        // accumulation: all 16 old values before any is stored, so
+                        // that a lane waits for one memory latency per block, not
+                        // 16. The pointer is opaque between the blocks and between
+                        // loads and stores: else 16 addresses are kept, for every
+                        // block in flight, and every fp32 instance needs 50 more
+                        // registers also where nothing accumulates (8192 x 8192 x
+                        // 4096 backward-data, 256 x 256 tiles: 16 % slower).
+                        typedef __attribute__((address_space(1))) float GlobalFloat;
+                        GlobalFloat *d = (GlobalFloat *)out + ((int64_t)rbase * ldo + col);
+                        float old[16];
+                        asm volatile("" : "+v"(d) : : "memory");
 #pragma unroll
                         for (int r = 0; r < 16; ++r) {
-                            const int row = rbase + 8 * (r >> 2) + (r & 3);
-                            old[r] = inb(row, g.m) ? reinterpret_cast<const float *>(
-                                                         out)[(int64_t)row * ldo + col]
-                                                   : 0.f;
+                            const int dr = 8 * (r >> 2) + (r & 3);
+                            old[r] = inb(rbase + dr, g.m) ? d[dr * ldo] : 0.f;
                         }
+                        asm volatile("" : "+v"(d) : : "memory");
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int dr = 8 * (r >> 2) + (r & 3);
+                            if (inb(rbase + dr, g.m)) d[dr * ldo] = old[r] + acc[i][j][r];
+                        }
+                        continue;
                     }
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int row = rbase + 8 * (r >> 2) + (r & 3);
                         if (inb(row, g.m)) {
-                            if constexpr (F32 && ACC) {
-                                reinterpret_cast<float *>(out)[(int64_t)row * ldo + col] =
-                                    old[r] + acc[i][j][r];
-                            } else if constexpr (F32 && PART)
+                            if constexpr (F32 && PART)
                                 st_part(part_rsrc(out), (int64_t)row * ldo + col, acc[i][j][r]);
                             else if constexpr (F32)
                                 st_nt(reinterpret_cast<float *>(out) + (int64_t)row * ldo + col,
