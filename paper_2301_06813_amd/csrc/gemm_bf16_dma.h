@@ -883,14 +883,16 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                 const int col = on0 + wn * WN + j * 32 + (lane & 31);
                 const int rbase = om0 + wm * WM + i * 32 + 4 * (lane >> 5);
                 if (inb(col, g.n)) {
-                    if constexpr (F32 && ACC) {
+                    if constexpr (F32 && ACC && BM * BN < 128 * 128) {
                         // accumulation: all 16 old values before any is stored, so
                         // that a lane waits for one memory latency per block, not
-                        // 16. The pointer is opaque between the blocks and between
+                        // 16 (micro-batch pairs of 64 x 128 tiles 23.7 -> 15.2 us).
+                        // The pointer is opaque between the blocks and between
                         // loads and stores: else 16 addresses are kept, for every
-                        // block in flight, and every fp32 instance needs 50 more
-                        // registers also where nothing accumulates (8192 x 8192 x
-                        // 4096 backward-data, 256 x 256 tiles: 16 % slower).
+                        // block in flight, in 50 more registers. Larger tiles keep
+                        // the element-wise form below: beside the batched one the
+                        // main loop of the 256 x 256 backward-data instance gets
+                        // four more waits also where nothing accumulates.
                         typedef __attribute__((address_space(1))) float GlobalFloat;
                         GlobalFloat *d = (GlobalFloat *)out + ((int64_t)rbase * ldo + col);
                         float old[16];
@@ -912,7 +914,10 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                     for (int r = 0; r < 16; ++r) {
                         const int row = rbase + 8 * (r >> 2) + (r & 3);
                         if (inb(row, g.m)) {
-                            if constexpr (F32 && PART)
+                            if constexpr (F32 && ACC) {
+                                float *d = reinterpret_cast<float *>(out) + (int64_t)row * ldo + col;
+                                *d = *d + acc[i][j][r];
+                            } else if constexpr (F32 && PART)
                                 st_part(part_rsrc(out), (int64_t)row * ldo + col, acc[i][j][r]);
                             else if constexpr (F32)
                                 st_nt(reinterpret_cast<float *>(out) + (int64_t)row * ldo + col,
