@@ -547,7 +547,10 @@ int sbp_profile_end(float *us, char *names, int name_len);
  * item; the grouped backward launch always runs one per item). A call whose
  * operands the pipelined kernel cannot read runs the generic kernel, where
  * 256x256 and 256x192 become 256x128; splits are clamped to the reduction
- * blocks and to the call's workspace. tile_m = 0 clears the override.
+ * blocks and to the call's workspace. An unsplit product that is added to its
+ * output (SBP_ACCUMULATE) exists for codes 1 (256x256, 256x192, 64x64), 4, 12
+ * and 2 only: under another code it runs code 4 or 1 of its tile, else 2.
+ * tile_m = 0 clears the override.
  * Errors: SBP_ERR_SHAPE for a (tile, kernel) pair not listed above,
  * splits < 1, or wgs_per_cu outside [0, 8]. */
 int sbp_set_plan_override(int32_t tile_m, int32_t tile_n, int32_t splits,

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "gemm_bf16_kernel.h"
+#include "model_instances.h"
 
 namespace sbpk {
 
@@ -409,9 +410,30 @@ __device__ __forceinline__ void store_staged(const float *tile, void *C, int64_t
     static_assert((BM * CPR) % NT_ == 0, "tile not divisible among threads");
     if constexpr (ACC) {
         // the old contents of U chunks are loaded before any is stored, so that
-        // a thread waits for one memory latency per U chunks
+        // a thread waits for one memory latency per U chunks; tiles inside the
+        // output keep no bounds checks between the two
         constexpr int U = ITER < 4 ? ITER : 4;
         float *const base = reinterpret_cast<float *>(C);
+        if (vec && m0 >= 0 && m0 + BM <= m && n0 >= 0 && n0 + BN <= n) {
+            for (int it = 0; it < ITER; it += U) {
+                f32x4 v[U];
+                float *dst[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = (it + u) * NT_ + tid;
+                    dst[u] = base + (int64_t)(m0 + q / CPR) * ldc + n0 + (q % CPR) * EPC;
+                    v[u] = *reinterpret_cast<const f32x4_any *>(dst[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = (it + u) * NT_ + tid;
+                    *reinterpret_cast<f32x4_any *>(dst[u]) =
+                        v[u] +
+                        *reinterpret_cast<const f32x4 *>(tile + q / CPR * LD + q % CPR * EPC);
+                }
+            }
+            return;
+        }
         for (int it = 0; it < ITER; it += U) {
             f32x4 v[U];
 #pragma unroll
@@ -493,13 +515,16 @@ __device__ __forceinline__ void store_staged(const float *tile, void *C, int64_t
     }
 }
 
-// Epilogue variants of the tile body.
+// How the tile body treats an output that the product is added to. The plain
+// forms hold no accumulating code: as a run-time branch beside the plain stores
+// it cost the fp32 64 x 64, 64 x 128 and 128 x 64 direct instances 35 to 41
+// spilled scalar registers and up to a sixth of a launch also where nothing
+// accumulated (1024 x 4096 x 1024 backward-data on 64 x 64 two-stage tiles 19.0 us,
+// without it 16.3).
 enum : int {
-    EPI_DIRECT = 0,   // each lane stores its MFMA elements (4-byte / 2-byte stores)
-    EPI_STAGED = 1,   // tile staged in LDS, stored as 16-byte row chunks by all threads
-    EPI_ROWQ = 2      // MFMA operands swapped so that each lane holds 4 consecutive
-                      // outputs of one row: 16-byte (fp32) / 8-byte (bf16) stores
-                      // straight from registers, no LDS and no wait
+    ACC_NONE = 0,   // never accumulates
+    ACC_SOME = 1,   // adds where g.accumulate (either product of a pair)
+    ACC_ALL = 2     // always adds; unsplit
 };
 
 // One work item (an output tile and a reduction split) of a product, by the
@@ -513,7 +538,7 @@ enum : int {
 // LDS, so the next item may refill it; after the direct epilogue the caller
 // must synchronise the workgroup first.
 template <int BM, int BN, int BKD, int NS, int WGM, int WGN, int KG, int EPI, bool A_KMAJ,
-          bool B_KMAJ, bool OUT_F32, bool SHIFT, bool REG = false, class Args>
+          bool B_KMAJ, bool OUT_F32, bool SHIFT, bool REG = false, int ACCUM = ACC_NONE, class Args>
 __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *smem) {
     constexpr int NSW = WGM * WGN;                // waves per reduction group
     constexpr int NW = NSW * KG;
@@ -695,7 +720,8 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
     // Split reduction: this workgroup's fp32 partial goes to slice `split`
     // of the workspace (m x n, row stride partial_ld(n)); a separate kernel
     // adds the slices in split order.
-    const bool partial = g.splits > 1;
+    const bool partial = ACCUM != ACC_ALL && g.splits > 1;
+    const bool add = ACCUM == ACC_ALL || (ACCUM == ACC_SOME && g.accumulate);
     const int ldw = (int)sbpi::partial_ld(g.n);
     float *const ws_out = g.ws + (size_t)split * (size_t)g.m * (size_t)ldw;
     const bool ws_vec = shift_n(g) % 4 == 0;
@@ -741,13 +767,12 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
     }
 
     if constexpr (EPI == EPI_ROWQ) {
+        static_assert(ACCUM == ACC_NONE, "no accumulating row-quad form");
         // lane owns row r = lane % 32 of each 32 x 32 block and, for register
         // quad q, columns 8 q + 4 (lane / 32) + 0..3
         // part_tag: out is a split partial slice (st_part)
-        auto store_all = [&](auto f32_tag, auto acc_tag, void *out, int64_t ldo, bool vec,
-                             auto part_tag) {
+        auto store_all = [&](auto f32_tag, void *out, int64_t ldo, bool vec, auto part_tag) {
             constexpr bool F32 = decltype(f32_tag)::value;
-            constexpr bool ACC = decltype(acc_tag)::value;
             constexpr bool PART = decltype(part_tag)::value;
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
@@ -755,19 +780,6 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                 if (!inb(row, g.m)) continue;
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
-                    // accumulation: all four old quads before any is stored
-                    f32x4 old[4];
-                    if constexpr (ACC) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int col = on0 + wn * WN + j * 32 + 8 * q + 4 * (lane >> 5);
-                            const float *src =
-                                reinterpret_cast<const float *>(out) + (int64_t)row * ldo + col;
-                            old[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-                            if (vec && (!SHIFT || col >= 0) && col + 4 <= g.n)
-                                old[q] = *reinterpret_cast<const f32x4 *>(src);
-                        }
-                    }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int col = on0 + wn * WN + j * 32 + 8 * q + 4 * (lane >> 5);
@@ -777,9 +789,7 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                             if (vec && (!SHIFT || col >= 0) && col + 4 <= g.n) {
                                 f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1],
                                            acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                                if constexpr (ACC) {
-                                    *reinterpret_cast<f32x4 *>(dst) = old[q] + v;
-                                } else if constexpr (PART) {
+                                if constexpr (PART) {
                                     st_part(part_rsrc(out), (int64_t)row * ldo + col, v);
                                 } else {
                                     st_nt(reinterpret_cast<f32x4 *>(dst), v);
@@ -788,9 +798,7 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
 #pragma unroll
                                 for (int e = 0; e < 4; ++e)
                                     if (inb(col + e, g.n)) {
-                                        if constexpr (ACC)
-                                            dst[e] = dst[e] + acc[i][j][4 * q + e];
-                                        else if constexpr (PART)
+                                        if constexpr (PART)
                                             st_part(part_rsrc(out), (int64_t)row * ldo + col + e,
                                                     acc[i][j][4 * q + e]);
                                         else
@@ -819,14 +827,10 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
             }
         };
         if (partial)
-            store_all(std::true_type{}, std::false_type{}, ws_out, (int64_t)ldw, ws_vec,
-                      std::true_type{});
-        else if (OUT_F32 && g.accumulate)
-            store_all(std::integral_constant<bool, OUT_F32>{}, std::integral_constant<bool, OUT_F32>{},
-                      Cb, g.ldc, (bool)g.vec_c4, std::false_type{});
+            store_all(std::true_type{}, ws_out, (int64_t)ldw, ws_vec, std::true_type{});
         else
-            store_all(std::integral_constant<bool, OUT_F32>{}, std::false_type{}, Cb, g.ldc,
-                      (bool)g.vec_c4, std::false_type{});
+            store_all(std::integral_constant<bool, OUT_F32>{}, Cb, g.ldc, (bool)g.vec_c4,
+                      std::false_type{});
         return;
     }
 
@@ -866,8 +870,8 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
         if (partial)
             store_staged<BM, BN, LD, 64 * NW, true, false, SHIFT, true>(tile, ws_out, ldw, g.m, g.n,
                                                                   om0, on0, ws_vec, tid);
-        else if (OUT_F32 && g.accumulate)
-            store_staged<BM, BN, LD, 64 * NW, OUT_F32, OUT_F32, SHIFT>(
+        else if (OUT_F32 && add)
+            store_staged<BM, BN, LD, 64 * NW, OUT_F32, OUT_F32 && ACCUM != ACC_NONE, SHIFT>(
                 tile, Cb, g.ldc, g.m, g.n, om0, on0, REG || g.vec_c4, tid);
         else
             store_staged<BM, BN, LD, 64 * NW, OUT_F32, false, SHIFT>(
@@ -888,30 +892,39 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                 const int col = on0 + wn * WN + j * 32 + (lane & 31);
                 const int rbase = om0 + wm * WM + i * 32 + 4 * (lane >> 5);
                 if (inb(col, g.n)) {
-                    if constexpr (F32 && ACC && BM * BN < 128 * 128) {
-                        // accumulation: all 16 old values before any is stored, so
-                        // that a lane waits for one memory latency per block, not
-                        // 16 (micro-batch pairs of 64 x 128 tiles 23.7 -> 15.2 us).
-                        // The pointer is opaque between the blocks and between
-                        // loads and stores: else 16 addresses are kept, for every
-                        // block in flight, in 50 more registers. Larger tiles keep
-                        // the element-wise form below: beside the batched one the
-                        // main loop of the 256 x 256 backward-data instance gets
-                        // four more waits also where nothing accumulates.
+                    if constexpr (F32 && ACC) {
+                        // all 16 old values before any is stored, so that a lane
+                        // waits for one memory latency per block, not 16 (a 2048 x
+                        // 2048 gradient over 512 on 128 x 128 two-stage tiles 18.3
+                        // -> 11.3 us; storing it takes 10.5). The pointer is opaque
+                        // between the blocks and between loads and stores: else 16
+                        // addresses are kept, for every block in flight, in 50 more
+                        // registers. Blocks cut by the last row load from it again
+                        // instead, so that no lane mask is kept from load to store.
                         typedef __attribute__((address_space(1))) float GlobalFloat;
-                        GlobalFloat *d = (GlobalFloat *)out + ((int64_t)rbase * ldo + col);
                         float old[16];
-                        asm volatile("" : "+v"(d) : : "memory");
+                        const int r0 = __builtin_amdgcn_readfirstlane(om0 + wm * WM + i * 32);
+                        if ((!SHIFT || r0 >= 0) && r0 + 32 <= g.m) {
+                            GlobalFloat *d = (GlobalFloat *)out + ((int64_t)rbase * ldo + col);
+                            asm volatile("" : "+v"(d) : : "memory");
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int dr = 8 * (r >> 2) + (r & 3);
-                            old[r] = inb(rbase + dr, g.m) ? d[dr * ldo] : 0.f;
+                            for (int r = 0; r < 16; ++r) old[r] = d[(8 * (r >> 2) + (r & 3)) * ldo];
+                            asm volatile("" : "+v"(d) : : "memory");
+#pragma unroll
+                            for (int r = 0; r < 16; ++r)
+                                d[(8 * (r >> 2) + (r & 3)) * ldo] = old[r] + acc[i][j][r];
+                            continue;
                         }
-                        asm volatile("" : "+v"(d) : : "memory");
+                        GlobalFloat *const c = (GlobalFloat *)out + col;
 #pragma unroll
                         for (int r = 0; r < 16; ++r) {
-                            const int dr = 8 * (r >> 2) + (r & 3);
-                            if (inb(rbase + dr, g.m)) d[dr * ldo] = old[r] + acc[i][j][r];
+                            const int row = rbase + 8 * (r >> 2) + (r & 3);
+                            old[r] = c[(int64_t)max(0, min(row, g.m - 1)) * ldo];
+                        }
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int row = rbase + 8 * (r >> 2) + (r & 3);
+                            if (inb(row, g.m)) c[(int64_t)row * ldo] = old[r] + acc[i][j][r];
                         }
                         continue;
                     }
@@ -919,10 +932,7 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
                     for (int r = 0; r < 16; ++r) {
                         const int row = rbase + 8 * (r >> 2) + (r & 3);
                         if (inb(row, g.m)) {
-                            if constexpr (F32 && ACC) {
-                                float *d = reinterpret_cast<float *>(out) + (int64_t)row * ldo + col;
-                                *d = *d + acc[i][j][r];
-                            } else if constexpr (F32 && PART)
+                            if constexpr (F32 && PART)
                                 st_part(part_rsrc(out), (int64_t)row * ldo + col, acc[i][j][r]);
                             else if constexpr (F32)
                                 st_nt(reinterpret_cast<float *>(out) + (int64_t)row * ldo + col,
@@ -938,9 +948,10 @@ __device__ __forceinline__ void dma_tile_body(const Args &g, const int L, char *
     };
     if (partial)
         store_all(std::true_type{}, std::false_type{}, ws_out, (int64_t)ldw, std::true_type{});
-    else if (OUT_F32 && g.accumulate)
-        store_all(std::integral_constant<bool, OUT_F32>{}, std::integral_constant<bool, OUT_F32>{},
-                  Cb, g.ldc, std::false_type{});
+    else if (OUT_F32 && add)
+        store_all(std::integral_constant<bool, OUT_F32>{},
+                  std::integral_constant<bool, OUT_F32 && ACCUM != ACC_NONE>{}, Cb, g.ldc,
+                  std::false_type{});
     else
         store_all(std::integral_constant<bool, OUT_F32>{}, std::false_type{}, Cb, g.ldc,
                   std::false_type{});
@@ -957,7 +968,7 @@ template <bool SHIFT>
 using ArgsOf = typename std::conditional<SHIFT, GemmArgsShift, GemmArgs>::type;
 
 template <int BM, int BN, int BKD, int NS, int WGM, int WGN, int KG, int EPI, bool A_KMAJ,
-          bool B_KMAJ, bool OUT_F32, bool SHIFT = false>
+          bool B_KMAJ, bool OUT_F32, bool SHIFT = false, int ACCUM = ACC_NONE>
 __global__ __launch_bounds__(64 * WGM * WGN * KG,
                              (Occupancy<BM, BN, BKD, NS, WGM * WGN * KG, KG>::VALUE))
 void gemm_bf16_dma_kernel(ArgsOf<SHIFT> g) {
@@ -967,8 +978,8 @@ void gemm_bf16_dma_kernel(ArgsOf<SHIFT> g) {
         // a later item refills the pipeline's LDS: every wave must be done
         // reading it (the direct epilogue does not end with a barrier)
         if (EPI == EPI_DIRECT && v != (int)blockIdx.x) __syncthreads();
-        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, A_KMAJ, B_KMAJ, OUT_F32, SHIFT>(
-            g, remap_xcd(v, total), smem);
+        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, A_KMAJ, B_KMAJ, OUT_F32, SHIFT, false,
+                      ACCUM>(g, remap_xcd(v, total), smem);
     }
 }
 
@@ -981,12 +992,12 @@ void gemm_bf16_dma_kernel(ArgsOf<SHIFT> g) {
 // backward-data product 186 -> 32 us, backward-weight 70 -> 28 us; 3777 x 1801 x
 // 5504 backward-weight runs at 645 TFLOP/s.
 template <int BM, int BN, int WGM, int WGN, int KG, int EPI, bool A_KMAJ, bool B_KMAJ,
-          bool OUT_F32>
+          bool OUT_F32, int ACCUM = ACC_NONE>
 __global__ __launch_bounds__(64 * WGM * WGN * KG, (BM * BN > 64 * 128 ? 2 : 4))
 void gemm_bf16_reg_kernel(GemmArgs g) {
     __shared__ __attribute__((aligned(1024))) char smem[2 * DmaStage<BM, BN, 64, 2>::BYTES];
     const int total = g.tiles_m * g.tiles_n * g.splits * g.nbatch;
-    dma_tile_body<BM, BN, 64, 2, WGM, WGN, KG, EPI, A_KMAJ, B_KMAJ, OUT_F32, false, true>(
+    dma_tile_body<BM, BN, 64, 2, WGM, WGN, KG, EPI, A_KMAJ, B_KMAJ, OUT_F32, false, true, ACCUM>(
         g, remap_xcd(blockIdx.x, total), smem);
 }
 
@@ -999,7 +1010,7 @@ void gemm_bf16_reg_kernel(GemmArgs g) {
 // attention product are the same pair, batched, or (D_BKMAJ = false) a pair
 // whose first product has an n-major B: dQ = dS K beside dK = dS^T Q.
 template <int BM, int BN, int BKD, int NS, int WGM, int WGN, int KG, int EPI, bool OUTD_F32,
-          bool OUTW_F32, bool SHIFT = false, bool D_BKMAJ = true>
+          bool OUTW_F32, bool SHIFT = false, bool D_BKMAJ = true, int ACCUM = ACC_NONE>
 __global__ __launch_bounds__(64 * WGM * WGN * KG,
                              (Occupancy<BM, BN, BKD, NS, WGM * WGN * KG, KG>::VALUE))
 void gemm_bf16_dma_bwd_kernel(ArgsOf<SHIFT> gd, ArgsOf<SHIFT> gw, int data_first) {
@@ -1010,12 +1021,12 @@ void gemm_bf16_dma_bwd_kernel(ArgsOf<SHIFT> gd, ArgsOf<SHIFT> gw, int data_first
     const bool is_data = data_first ? (b < wd) : (b >= ww);
     if (is_data) {
         const int local = data_first ? b : b - ww;
-        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, true, D_BKMAJ, OUTD_F32, SHIFT>(
-            gd, remap_xcd(local, wd), smem);
+        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, true, D_BKMAJ, OUTD_F32, SHIFT, false,
+                      ACCUM>(gd, remap_xcd(local, wd), smem);
     } else {
         const int local = data_first ? b - wd : b;
-        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, false, false, OUTW_F32, SHIFT>(
-            gw, remap_xcd(local, ww), smem);
+        dma_tile_body<BM, BN, BKD, NS, WGM, WGN, KG, EPI, false, false, OUTW_F32, SHIFT, false,
+                      ACCUM>(gw, remap_xcd(local, ww), smem);
     }
 }
 

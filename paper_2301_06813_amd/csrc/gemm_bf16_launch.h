@@ -7,6 +7,7 @@
 
 #include "gemm.h"
 #include "gemm_bf16_dma.h"
+#include "model_instances.h"
 #include "profile.h"
 
 // Pipeline depth per tile (stages); defaults keep LDS within 160 KB.
@@ -18,9 +19,6 @@
 #endif
 #ifndef SBP_NS_128x64
 #define SBP_NS_128x64 4
-#endif
-#ifndef SBP_NS_64x64
-#define SBP_NS_64x64 4
 #endif
 
 namespace sbpi {
@@ -92,57 +90,65 @@ static inline int grid_of(const Plan &p, int items) {
     return std::max(8, cap / 8 * 8);
 }
 
-template <bool AK, bool BK_, bool OUTF>
+// ACCUM: ACC_NONE, or ACC_ALL for an unsplit product that is added to its output,
+// which the instances of SBP_MODEL_INSTANCES, the shifted ones and the generic
+// kernel's have.
+template <bool AK, bool BK_, bool OUTF, int ACCUM>
 static hipError_t launch_tile(const Plan &p, const sbpk::GemmArgsShift &as, int items,
                               hipStream_t s) {
     const sbpk::GemmArgs a = as;   // the unshifted kernels' arguments
     char name[192];
     const char *tf[2] = {"false", "true"};
+    const char *const end[2] = {ACCUM ? ", false, 2>" : ">", ACCUM ? ", true, 2>" : ", true>"};
     const int grid = grid_of(p, items);
-    if (p.dma && p.shift) {
-#define SBP_DMA_SHIFT_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                      \
+#define SBP_DMA_CASE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, SHIFT_, ARGS_)             \
     if (p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ && (p.ns == 0 || p.ns == NS_) &&          \
         p.kg == KG_ && p.epi == EPI_) {                                                     \
-        if (profiling()) snprintf(name, sizeof(name),                                                        \
-                 "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s, %s, true>",  \
-                 BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF]);    \
+        if (profiling())                                                                    \
+            snprintf(name, sizeof(name),                                                    \
+                     "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s, %s%s",   \
+                     BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF], \
+                     end[SHIFT_]);                                                          \
         return launch_kernel(                                                               \
             sbpk::gemm_bf16_dma_kernel<BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, AK, BK_, \
-                                       OUTF, true>,                                         \
-            name, dim3(grid), dim3(64 * WGM_ * WGN_ * KG_), s, as);                         \
+                                       OUTF, SHIFT_, ACCUM>,                                \
+            name, dim3(grid), dim3(64 * WGM_ * WGN_ * KG_), s, ARGS_);                      \
     }
-        SBP_DMA_SHIFT_INSTANCES(SBP_DMA_SHIFT_TILE)
-#undef SBP_DMA_SHIFT_TILE
-        return hipErrorInvalidValue;
-    }
+#define SBP_DMA_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_) \
+    SBP_DMA_CASE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, false, a)
+#define SBP_DMA_SHIFT_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_) \
+    SBP_DMA_CASE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, true, as)
 #define SBP_TILE(BM_, BN_, WGM_, WGN_, KG_, EPI_)                                            \
-    if (!p.dma && p.bm == BM_ && p.bn == BN_) {                                             \
-        if (profiling()) snprintf(name, sizeof(name), "gemm_bf16_reg_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s>", \
-                 BM_, BN_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF]);               \
+    if (p.bm == BM_ && p.bn == BN_) {                                                       \
+        if (profiling())                                                                    \
+            snprintf(name, sizeof(name),                                                    \
+                     "gemm_bf16_reg_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s%s", BM_, BN_, \
+                     WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF], ACCUM ? ", 2>" : ">"); \
         return launch_kernel(                                                               \
-            sbpk::gemm_bf16_reg_kernel<BM_, BN_, WGM_, WGN_, KG_, EPI_, AK, BK_, OUTF>,     \
+            sbpk::gemm_bf16_reg_kernel<BM_, BN_, WGM_, WGN_, KG_, EPI_, AK, BK_, OUTF,      \
+                                       ACCUM>,                                              \
             name, dim3(items), dim3(64 * WGM_ * WGN_ * KG_), s, a);                         \
     }
-#define SBP_DMA_TILE(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_)                            \
-    if (p.dma && p.bm == BM_ && p.bn == BN_ && p.bk == BKD_ &&                               \
-        (p.ns == 0 || p.ns == NS_) && p.kg == KG_ && p.epi == EPI_) {                       \
-        if (profiling()) snprintf(name, sizeof(name),                                                        \
-                 "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %d, %s, %s, %s>", BM_,   \
-                 BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, tf[AK], tf[BK_], tf[OUTF]);         \
-        return launch_kernel(                                                               \
-            sbpk::gemm_bf16_dma_kernel<BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_, AK, BK_, \
-                                       OUTF>,                                               \
-            name, dim3(grid), dim3(64 * WGM_ * WGN_ * KG_), s, a);                          \
+    if (p.dma && p.shift) {
+        SBP_DMA_SHIFT_INSTANCES(SBP_DMA_SHIFT_TILE)
+    } else if (p.dma) {
+        if constexpr (ACCUM == sbpk::ACC_NONE) {
+            SBP_DMA_INSTANCES(SBP_DMA_TILE)
+        } else {
+            SBP_MODEL_INSTANCES(SBP_DMA_TILE)
+        }
+    } else {
+        SBP_TILE(256, 128, 4, 2, 1, sbpk::EPI_DIRECT)
+        SBP_TILE(128, 256, 2, 4, 1, sbpk::EPI_DIRECT)
+        SBP_TILE(128, 128, 2, 4, 1, sbpk::EPI_STAGED)
+        SBP_TILE(128, 64, 2, 2, 2, sbpk::EPI_STAGED)
+        SBP_TILE(64, 128, 2, 2, 2, sbpk::EPI_STAGED)
+        SBP_TILE(64, 64, 2, 2, 2, sbpk::EPI_STAGED)
     }
-    SBP_TILE(256, 128, 4, 2, 1, sbpk::EPI_DIRECT)
-    SBP_TILE(128, 256, 2, 4, 1, sbpk::EPI_DIRECT)
-    SBP_TILE(128, 128, 2, 4, 1, sbpk::EPI_STAGED)
-    SBP_TILE(128, 64, 2, 2, 2, sbpk::EPI_STAGED)
-    SBP_TILE(64, 128, 2, 2, 2, sbpk::EPI_STAGED)
-    SBP_TILE(64, 64, 2, 2, 2, sbpk::EPI_STAGED)
-    SBP_DMA_INSTANCES(SBP_DMA_TILE)
 #undef SBP_TILE
+#undef SBP_DMA_SHIFT_TILE
 #undef SBP_DMA_TILE
+#undef SBP_DMA_CASE
     return hipErrorInvalidValue;
 }
 
@@ -201,9 +207,11 @@ static hipError_t launch_orient(const Gemm &g, const Plan &p, float *ws, hipStre
     const sbpk::GemmArgsShift a = make_args(g, p, ws);
     const int items = a.tiles_m * a.tiles_n * a.splits * a.nbatch;
     // with splits the GEMM writes fp32 partials, whatever the output dtype
-    hipError_t e = (g.out_dtype == DT_F32 || p.splits > 1)
-                       ? launch_tile<AK, BK_, true>(p, a, items, s)
-                       : launch_tile<AK, BK_, false>(p, a, items, s);
+    hipError_t e = g.accumulate && p.splits == 1
+                       ? launch_tile<AK, BK_, true, sbpk::ACC_ALL>(p, a, items, s)
+                   : (g.out_dtype == DT_F32 || p.splits > 1)
+                       ? launch_tile<AK, BK_, true, sbpk::ACC_NONE>(p, a, items, s)
+                       : launch_tile<AK, BK_, false, sbpk::ACC_NONE>(p, a, items, s);
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_split_reduce(g, p.splits, ws, s);
 }

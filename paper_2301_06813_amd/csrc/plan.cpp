@@ -13,6 +13,7 @@
 #include <unordered_map>
 
 #include "gemm.h"
+#include "model_instances.h"
 
 namespace sbpi {
 
@@ -43,7 +44,7 @@ struct PipeClass {
     int bm, bn, code, res;
     double step[3], epi;
 };
-const PipeClass kPipe[] = {
+constexpr PipeClass kPipe[] = {
     {64, 64, 1, 2, {0.325, 0.203, 0.203}, 0.77},    {64, 64, 4, 5, {0.378, 0.255, 0.184}, 0.48},
     {64, 64, 12, 1, {0.195, 0.195, 0.195}, 1.99},   {64, 128, 4, 3, {0.521, 0.311, 0.278}, 0.89},
     {64, 128, 12, 1, {0.338, 0.338, 0.338}, 2.58},  {128, 64, 4, 3, {0.521, 0.311, 0.278}, 0.89},
@@ -72,28 +73,59 @@ thread_local int ov_bwd_mode = 0, ov_bwd_splits_w = 1;   // see set_bwd_override
 struct Instance {
     int code, bm, bn, ns, kg, epi, bk = 64;
 };
-constexpr int E_DIRECT = 0, E_STAGED = 1, E_ROWQ = 2;   // = sbpk::EPI_*
-const Instance kInstances[] = {
-    {1, 256, 256, 0, 1, E_DIRECT}, {1, 256, 192, 0, 1, E_DIRECT},
-    {1, 256, 128, 0, 1, E_DIRECT}, {1, 128, 256, 0, 1, E_DIRECT},
-    {1, 128, 128, 0, 1, E_DIRECT}, {1, 128, 64, 0, 1, E_DIRECT},  {1, 64, 128, 0, 1, E_DIRECT},
-    {1, 64, 64, 0, 1, E_DIRECT},   {4, 128, 128, 2, 1, E_DIRECT}, {5, 256, 128, 0, 2, E_STAGED},
-    {5, 128, 256, 0, 2, E_STAGED}, {5, 128, 128, 0, 2, E_STAGED}, {6, 256, 256, 0, 1, E_ROWQ},
-    {6, 128, 128, 2, 1, E_ROWQ},   {7, 256, 128, 0, 2, E_ROWQ},   {7, 128, 256, 0, 2, E_ROWQ},
-    {7, 128, 128, 0, 2, E_ROWQ},   {8, 256, 256, 5, 1, E_DIRECT, 32},
-    {9, 256, 128, 6, 2, E_STAGED, 32}, {9, 128, 256, 6, 2, E_STAGED, 32},
-    {9, 128, 128, 8, 2, E_STAGED, 32}, {10, 128, 128, 2, 2, E_STAGED},
-    {4, 128, 64, 2, 1, E_DIRECT},      {4, 64, 128, 2, 1, E_DIRECT},
-    {4, 64, 64, 2, 1, E_DIRECT},       {11, 128, 64, 6, 1, E_DIRECT},
-    {11, 64, 128, 6, 1, E_DIRECT},     {11, 64, 64, 8, 1, E_DIRECT},
-    {5, 128, 64, 0, 2, E_STAGED},      {5, 64, 128, 0, 2, E_STAGED},
-    {5, 64, 64, 0, 2, E_STAGED},       {7, 128, 64, 0, 2, E_ROWQ},
-    {7, 64, 128, 0, 2, E_ROWQ},        {7, 64, 64, 0, 2, E_ROWQ},
-    {12, 128, 128, 2, 2, E_STAGED, 128}, {12, 128, 64, 3, 2, E_STAGED, 128},
-    {12, 64, 128, 3, 2, E_STAGED, 128},  {12, 64, 64, 4, 2, E_STAGED, 128},
-    {13, 128, 128, 2, 2, E_ROWQ, 128},   {13, 128, 64, 3, 2, E_ROWQ, 128},
-    {13, 64, 128, 3, 2, E_ROWQ, 128},    {13, 64, 64, 4, 2, E_ROWQ, 128},
+using sbpk::EPI_DIRECT;
+using sbpk::EPI_ROWQ;
+using sbpk::EPI_STAGED;
+
+constexpr Instance kInstances[] = {
+    {1, 256, 256, 0, 1, EPI_DIRECT}, {1, 256, 192, 0, 1, EPI_DIRECT},
+    {1, 256, 128, 0, 1, EPI_DIRECT}, {1, 128, 256, 0, 1, EPI_DIRECT},
+    {1, 128, 128, 0, 1, EPI_DIRECT}, {1, 128, 64, 0, 1, EPI_DIRECT},  {1, 64, 128, 0, 1, EPI_DIRECT},
+    {1, 64, 64, 0, 1, EPI_DIRECT},   {4, 128, 128, 2, 1, EPI_DIRECT}, {5, 256, 128, 0, 2, EPI_STAGED},
+    {5, 128, 256, 0, 2, EPI_STAGED}, {5, 128, 128, 0, 2, EPI_STAGED}, {6, 256, 256, 0, 1, EPI_ROWQ},
+    {6, 128, 128, 2, 1, EPI_ROWQ},   {7, 256, 128, 0, 2, EPI_ROWQ},   {7, 128, 256, 0, 2, EPI_ROWQ},
+    {7, 128, 128, 0, 2, EPI_ROWQ},   {8, 256, 256, 5, 1, EPI_DIRECT, 32},
+    {9, 256, 128, 6, 2, EPI_STAGED, 32}, {9, 128, 256, 6, 2, EPI_STAGED, 32},
+    {9, 128, 128, 8, 2, EPI_STAGED, 32}, {10, 128, 128, 2, 2, EPI_STAGED},
+    {4, 128, 64, 2, 1, EPI_DIRECT},      {4, 64, 128, 2, 1, EPI_DIRECT},
+    {4, 64, 64, 2, 1, EPI_DIRECT},       {11, 128, 64, 6, 1, EPI_DIRECT},
+    {11, 64, 128, 6, 1, EPI_DIRECT},     {11, 64, 64, 8, 1, EPI_DIRECT},
+    {5, 128, 64, 0, 2, EPI_STAGED},      {5, 64, 128, 0, 2, EPI_STAGED},
+    {5, 64, 64, 0, 2, EPI_STAGED},       {7, 128, 64, 0, 2, EPI_ROWQ},
+    {7, 64, 128, 0, 2, EPI_ROWQ},        {7, 64, 64, 0, 2, EPI_ROWQ},
+    {12, 128, 128, 2, 2, EPI_STAGED, 128}, {12, 128, 64, 3, 2, EPI_STAGED, 128},
+    {12, 64, 128, 3, 2, EPI_STAGED, 128},  {12, 64, 64, 4, 2, EPI_STAGED, 128},
+    {13, 128, 128, 2, 2, EPI_ROWQ, 128},   {13, 128, 64, 3, 2, EPI_ROWQ, 128},
+    {13, 64, 128, 3, 2, EPI_ROWQ, 128},    {13, 64, 64, 4, 2, EPI_ROWQ, 128},
 };
+
+// kPipe names each instance of SBP_MODEL_INSTANCES (those with the grouped
+// attention launch and the accumulating form) once, and no other.
+constexpr bool model_lists_agree() {
+    struct Row {
+        int bm, bn, bk, ns, kg, epi;
+    };
+#define SBP_ROW(BM_, BN_, BKD_, NS_, WGM_, WGN_, KG_, EPI_) {BM_, BN_, BKD_, NS_, KG_, EPI_},
+    const Row rows[] = {SBP_MODEL_INSTANCES(SBP_ROW)};
+#undef SBP_ROW
+    constexpr int N = sizeof(rows) / sizeof(rows[0]);
+    bool used[N] = {};
+    int n = 0;
+    for (const PipeClass &c : kPipe)
+        for (const Instance &i : kInstances) {
+            if (i.code != c.code || i.bm != c.bm || i.bn != c.bn) continue;
+            for (int r = 0; r < N; ++r)
+                if (rows[r].bm == i.bm && rows[r].bn == i.bn && rows[r].bk == i.bk &&
+                    (i.ns == 0 || rows[r].ns == i.ns) && rows[r].kg == i.kg &&
+                    rows[r].epi == i.epi) {
+                    n += !used[r];
+                    used[r] = true;
+                    break;   // the first match is the one launched
+                }
+        }
+    return n == N && n == (int)(sizeof(kPipe) / sizeof(kPipe[0]));
+}
+static_assert(model_lists_agree(), "kPipe and SBP_MODEL_INSTANCES list different instances");
 
 // Plans measured fastest on MI355X for the local products of the paper's
 // workloads (generated by paper_2301_06813_amd/tune.py): orientation, fp32
@@ -132,9 +164,9 @@ struct ShiftInstance {
     int bm, bn, bk, ns, kg, epi;
 };
 const ShiftInstance kShiftInstances[] = {
-    {64, 64, 64, 0, 1, E_DIRECT},     {128, 128, 64, 2, 1, E_DIRECT},
-    {64, 64, 128, 4, 2, E_STAGED},    {128, 64, 128, 3, 2, E_STAGED},
-    {64, 128, 128, 3, 2, E_STAGED},   {128, 128, 128, 2, 2, E_STAGED},
+    {64, 64, 64, 0, 1, EPI_DIRECT},     {128, 128, 64, 2, 1, EPI_DIRECT},
+    {64, 64, 128, 4, 2, EPI_STAGED},    {128, 64, 128, 3, 2, EPI_STAGED},
+    {64, 128, 128, 3, 2, EPI_STAGED},   {128, 128, 128, 2, 2, EPI_STAGED},
 };
 
 bool shift_capable(int bm, int bn, int bk, int ns, int kg, int epi) {
@@ -253,6 +285,11 @@ static bool pipe_class(int bm, int bn, int code) {
     return false;
 }
 
+// Whether plan p adds to its output in the GEMM itself, which only the model's
+// instances (and the generic kernel) have a form for; a split plan's reduction
+// does it.
+static bool adds(const Gemm &g, const Plan &p) { return g.accumulate && p.splits == 1; }
+
 bool tile_supported(int bm, int bn, bool dma) {
     if (dma) {
         return find_instance(1, bm, bn) != nullptr;
@@ -335,13 +372,15 @@ static Plan plan_uncached(const Gemm &g);
 static Plan plan_model(const Gemm &g, double *time);
 
 // Tuned entry of product g under pipelined-kernel mode `mode` (nullptr if none).
+// The rows were measured storing their outputs: an unsplit one does not hold for
+// a product that is added to its output (a split one's reduction does that).
 static const Tuned *tuned_for(const Gemm &g, int mode) {
     if (g.in_dtype != DT_BF16) return nullptr;
     const int f32 = g.out_dtype == DT_F32 ? 1 : 0;
     for (const Tuned &t : kTuned) {
         if (t.orient < 0) break;
         if (t.orient == g.orient && t.out_f32 == f32 && t.m == g.m && t.n == g.n && t.k == g.k &&
-            t.dma == mode && t.nbatch == g.nbatch())
+            t.dma == mode && t.nbatch == g.nbatch() && !(g.accumulate && t.splits == 1))
             return &t;
     }
     return nullptr;
@@ -442,6 +481,7 @@ static bool grouped_plan(const Gemm &gd, const Gemm &gw, const Instance *in, int
         p = Plan{bm, bn, 1, 1, true, in->ns, in->kg, in->epi, 0, in->bk};
         p.shift = sh;
         split_of(kblocks(g.k), w ? sw : sd, &p.splits, &p.kblk_per_split);
+        if (adds(g, p) && !pipe_class(bm, bn, in->code)) return false;
     }
     // a batched product is never split, and all work items fit a 31-bit index
     if ((gd.nbatch() > 1 && pd->splits > 1) || (gw.nbatch() > 1 && pw->splits > 1)) return false;
@@ -474,6 +514,7 @@ static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw
         const int fd = gd.out_dtype == DT_F32, fw = gw.out_dtype == DT_F32;
         for (const TunedBwd &t : kTunedBwd) {
             if (t.md < 0 || gd.nbatch() > 1 || attn) break;
+            if ((gd.accumulate && t.sd == 1) || (gw.accumulate && t.sw == 1)) continue;
             if (t.md == gd.m && t.nd == gd.n && t.kd == gd.k && t.fd == fd && t.mw == gw.m &&
                 t.nw == gw.n && t.kw == gw.k && t.fw == fw) {
                 const Instance *in = find_instance(t.code, t.bm, t.bn);
@@ -485,7 +526,8 @@ static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw
         }
         // measured plans of both products: they run as measured, one after the
         // other (batched pairs were measured without a grouped form)
-        if (gd.nbatch() == 1 && tuned_for(gd, dma_mode(gd)) && tuned_for(gw, dma_mode(gw))) return false;
+        if (gd.nbatch() == 1 && tuned_for(gd, dma_mode(gd)) && tuned_for(gw, dma_mode(gw)))
+            return false;
     }
     const bool sh = dma_mode(gd) == 2 || dma_mode(gw) == 2;
     if (ov_bm != 0) {
@@ -500,6 +542,8 @@ static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw
         if (sh && !shift_capable(*pd)) return false;
         pd->shift = pw->shift = sh;
         pd->occ = pw->occ = 0;   // the grouped launch runs one workgroup per item
+        if ((adds(gd, *pd) || adds(gw, *pw)) && !pipe_class(pd->bm, pd->bn, kernel_code(*pd)))
+            return false;
         return (double)plan_ws_floats(gd, *pd) + (double)plan_ws_floats(gw, *pw) <=
                ws_budget(gd);
     }
@@ -632,6 +676,22 @@ static Plan plan_uncached(const Gemm &g) {
         split_of(kb_total, ov_splits, &p.splits, &p.kblk_per_split);
         while (p.splits > 1 && !fits_ws(g, p.splits))
             split_of(kb_total, p.splits - 1, &p.splits, &p.kblk_per_split);
+        if (use_dma && adds(g, p) && !pipe_class(p.bm, p.bn, in->code)) {
+            // no accumulating form: the tile's model instance, or the generic kernel
+            const int code = pipe_class(p.bm, p.bn, 4) ? 4 : 1;
+            const Instance *a = find_instance(code, p.bm, p.bn);
+            if (pipe_class(p.bm, p.bn, code) &&
+                (mode == 1 || shift_capable(p.bm, p.bn, a->bk, a->ns, a->kg, a->epi))) {
+                p.ns = a->ns;
+                p.kg = a->kg;
+                p.epi = a->epi;
+                p.bk = a->bk;
+            } else {
+                Plan q{p.bm, tile_supported(p.bm, p.bn, false) ? p.bn : 128, 1, p.kblk_per_split,
+                       false};
+                return q;
+            }
+        }
         return p;
     }
     if (const Tuned *t = tuned_for(g, mode)) {
@@ -652,8 +712,8 @@ static Plan plan_uncached(const Gemm &g) {
             if (fits_ws(g, p.splits)) return p;
         }
     }
-    double t;
-    return dma ? plan_model(g, &t) : plan_generic(g);
+    double time;
+    return dma ? plan_model(g, &time) : plan_generic(g);
 }
 
 // The pipelined plan the model expects to be fastest, and its time in us.

@@ -87,7 +87,20 @@ def _accumulate_case(op, sig, p, r, X, W, dY, Xh, Wh, dYh, seed):
 # (tile, kernel, splits) plans that reach every epilogue: direct, staged,
 # row-quad, the generic kernel, and the split reduction
 ACC_PLANS = [None, ((128, 128), 1, 1), ((128, 128), 1, 3), ((128, 128), 5, 1), ((64, 64), 7, 1),
-             ((256, 256), 6, 1), ((128, 128), 2, 1), ((64, 64), 2, 2)]
+             ((256, 256), 6, 1), ((128, 128), 2, 1), ((64, 64), 2, 2), ((64, 64), 1, 1),
+             ((64, 64), 4, 1), ((64, 128), 4, 1), ((128, 64), 4, 1), ((128, 128), 4, 1),
+             ((64, 64), 12, 1), ((64, 128), 12, 1), ((128, 64), 12, 1), ((128, 128), 12, 1),
+             ((256, 192), 1, 1), ((256, 256), 1, 1), ((256, 128), 1, 1), ((128, 256), 2, 1)]
+# the pipelined instances with an accumulating form; others add in a form of the
+# same tile's
+ACC_FORMS = {(64, 64): (1, 4, 12), (64, 128): (4, 12), (128, 64): (4, 12), (128, 128): (4, 12),
+             (256, 192): (1,), (256, 256): (1,)}
+
+
+def _accumulates(names):
+    # a GEMM kernel in its accumulating form, or the reduction that adds
+    return any(n.endswith((", 1>", ", 2>")) and n.startswith("gemm_") for n in names) or \
+        any(n.startswith("split_reduce") for n in names)
 
 
 @pytest.mark.parametrize("plan", ACC_PLANS, ids=[str(p_) for p_ in ACC_PLANS])
@@ -103,15 +116,31 @@ def test_exact_accumulate(plan):
             for sig in ("DP", "COL", "KS", "PB"):
                 for op in OPS:
                     say("accumulate", plan, p, r, sig, op)
-                    _accumulate_case(op, sig, p, r, X, W, dY, Xh, Wh, dYh, 310 + r)
+                    names = _kernel_names(lambda: _accumulate_case(op, sig, p, r, X, W, dY, Xh, Wh,
+                                                                   dYh, 310 + r))
+                    assert _accumulates(names), names
+                    if plan and code in ACC_FORMS.get(plan[0], ()) and splits == 1 and p == 2:
+                        # aligned shards: the instance itself, in its accumulating form
+                        assert any(n.startswith("gemm_bf16_dma_kernel<%d, %d, " % plan[0])
+                                   for n in names), names
+                        names = _kernel_names(lambda: linear.call(op, sig, p, r, X, W, dY))
+                        assert not _accumulates(names), names
     finally:
         sbp.sbp_set_plan_override(0, 0, 1)
 
 
-def test_exact_accumulate_grouped_backward():
+@pytest.mark.parametrize("shape,plan", [((256, 384, 320), (128, 128, 2, 1, 3)),
+                                        ((288, 400, 352), (64, 128, 1, 4, 1)),
+                                        ((288, 400, 352), (64, 64, 1, 4, 1)),
+                                        ((288, 400, 352), (128, 128, 1, 12, 1)),
+                                        ((288, 400, 352), (256, 256, 1, 1, 1)),
+                                        ((288, 400, 325), (64, 64, 1, 12, 1))], ids=str)
+def test_exact_accumulate_grouped_backward(shape, plan):
     # gradient accumulation over two micro-batches through the two-product
-    # call: dW = X1^T dY1 + X2^T dY2 (dX overwritten each time)
-    M, K, N = 256, 384, 320
+    # call: dW = X1^T dY1 + X2^T dY2 (dX overwritten each time). plan: tile,
+    # splits of dX, kernel, splits of dW
+    M, K, N = shape
+    bm, bn, sd, code, sw = plan
     X1, W, dY1 = _int_inputs(M, K, N, 400)
     X2, _, dY2 = _int_inputs(M, K, N, 410)
     for grouped in (1, 2):
@@ -122,13 +151,20 @@ def test_exact_accumulate_grouped_backward():
             dW = linear.alloc_out("bwd_weight", sig, p, r, M, K, N, X1.dtype, "cuda").float()
             dW.zero_()
             try:
-                sbp.sbp_set_plan_override(128, 128, 2, 1)
-                sbp.sbp_set_bwd_override(grouped, 3)
+                sbp.sbp_set_plan_override(bm, bn, sd, code)
+                sbp.sbp_set_bwd_override(grouped, sw)
                 for X, dY in ((X1, dY1), (X2, dY2)):
-                    linear.run_bwd_L(L, X, W, dY, dX, dW, accumulate_dw=True)
+                    names = _kernel_names(lambda: linear.run_bwd_L(L, X, W, dY, dX, dW,
+                                                                   accumulate_dw=True))
+                    assert _accumulates(names), names
                 torch.cuda.synchronize()
             finally:
                 sbp.sbp_set_plan_override(0, 0, 1)
+            one = any(n.startswith("gemm_bf16_dma_bwd_kernel<%d, %d, " % (bm, bn)) for n in names)
+            if grouped == 1 or N % 8:   # 325 columns: rows of no alignment, the generic kernel
+                assert not one, names
+            elif code in ACC_FORMS[bm, bn]:
+                assert one and (sw > 1 or names[0].endswith(", false, true, 1>")), names
             want = sum(oracle_full("bwd_weight", sig, p, r, *(inputs.host_bits(t) for t in
                                                               (X, W, dY)))
                        for X, dY in ((X1, dY1), (X2, dY2)))
