@@ -1,4 +1,5 @@
-// plan.cpp -- choice of output tile and reduction splits for the bf16 GEMM.
+// plan.cpp -- choice of output tile and reduction splits for the bf16 and fp32
+// GEMMs.
 //
 // A launch fills MI355X's 256 compute units only if it has enough
 // workgroups; many local shares of an SBP linear have small outputs and long
@@ -30,38 +31,55 @@ const GenericTile kGeneric[] = {
     {256, 128, 1.40e-6}, {128, 256, 1.40e-6}, {128, 128, 0.70e-6},
     {128, 64, 0.50e-6},  {64, 128, 0.50e-6},  {64, 64, 0.33e-6},
 };
-// Pipelined instances the model chooses among, with their measured times on
-// MI355X in us: a 64-wide reduction step of a work item alone on its compute
-// unit (`step[0]`), its share of the unit when two workgroups take turns there
-// (`step[1]`) and when three or more do (`step[2]`; `res` at most), and the
-// store of an fp32 output tile (`epi`; half for bf16). Fitted to 23 instances
-// x every split on 438 random products and 176 random backward pairs (extents
-// of 64 to 8192; 3 % rms); the instances left out were the fastest for almost
-// none of them. Over those the plans chosen take 3 % longer than the fastest
-// measured (products) and 4 % (pairs); the model of peak rates before this one
-// chose plans 8 % and 27 % longer.
+// Pipelined instances the model chooses among, with their times on MI355X in us:
+// a 64-wide reduction step of a work item alone on its compute unit (`step[0]`),
+// its share of the unit when two workgroups take turns there (`step[1]`) and when
+// three or more do (`step[2]`; `res` at most), and the end of an item, `end`:
+// what it takes however few items there are, then what the stores of an fp32 or
+// a bf16 tile add when the whole chip stores (in proportion below one item per
+// unit), what each adds where rows are not whole 64-byte blocks, and what loading
+// the old values adds where the product is added to its output.
+//
+// Fitted on 1483 random products and 1269 random backward pairs, each on up to 45
+// plans (measured from graphs of calls over three sets of operands in turn):
+// extents log-uniform in 64 .. 8192, 60 % multiples of 64 and the others of 8, up
+// to 2e11 operations; three orientations, fp32 and bf16 outputs, a third
+// accumulating, a fifth batched as in attention (2 to 128 items of 64 .. 2048 rows).
+// Fitted to the plans' times and to the time of the plan chosen: 9 % rms over
+// plans within 1.5 times of the best. On 688 products and 591 pairs not fitted, the
+// plan chosen takes 2.0 % (pairs 3.2 %) longer than the fastest measured on
+// average, 6 % (10 %) at the ninth decile, 15 % (29 %) at the 99th percentile and
+// 44 % (60 %) at worst. With the constants before, which knew neither rows cut by
+// 64-byte blocks, nor chips part filled, nor the accumulating forms, it took 6.0 %
+// (7.7 %) longer on average.
 struct PipeClass {
     int bm, bn, code, res;
-    double step[3], epi;
+    double step[3];
+    struct {
+        double least, f32, bf16, cut_f32, cut_bf16, add;
+    } end;
 };
 constexpr PipeClass kPipe[] = {
-    {64, 64, 1, 2, {0.325, 0.203, 0.203}, 0.77},    {64, 64, 4, 5, {0.378, 0.255, 0.184}, 0.48},
-    {64, 64, 12, 1, {0.195, 0.195, 0.195}, 1.99},   {64, 128, 4, 3, {0.521, 0.311, 0.278}, 0.89},
-    {64, 128, 12, 1, {0.338, 0.338, 0.338}, 2.58},  {128, 64, 4, 3, {0.521, 0.311, 0.278}, 0.89},
-    {128, 64, 12, 1, {0.338, 0.338, 0.338}, 2.58},  {128, 128, 4, 2, {0.646, 0.410, 0.410}, 1.89},
-    {128, 128, 12, 1, {0.491, 0.491, 0.491}, 3.51}, {256, 192, 1, 1, {1.145, 1.145, 1.145}, 3.83},
-    {256, 256, 1, 1, {1.487, 1.487, 1.487}, 4.36},
+    {64, 64, 1, 2, {0.394, 0.241, 0.241}, {0.65, 0.14, 0.16, 0.22, 0.22, 0.07}},
+    {64, 64, 4, 5, {0.418, 0.312, 0.233}, {0.13, 0.29, 0.24, 0.17, 0.15, 0.18}},
+    {64, 64, 12, 1, {0.207, 0.207, 0.207}, {1.34, 0.75, 0.54, 0.32, 0.54, 0.07}},
+    {64, 128, 4, 3, {0.760, 0.356, 0.339}, {0.79, 0.30, 0.24, 1.01, 0.58, 0.05}},
+    {64, 128, 12, 1, {0.409, 0.409, 0.409}, {1.78, 1.26, 0.51, 0.25, 0.64, 0.36}},
+    {128, 64, 4, 3, {0.755, 0.334, 0.309}, {0.60, 0.33, 0.21, 0.73, 0.22, 0.19}},
+    {128, 64, 12, 1, {0.367, 0.367, 0.367}, {1.87, 1.24, 0.59, 0.29, 0.70, 0.30}},
+    {128, 128, 4, 2, {0.792, 0.388, 0.388}, {2.07, 0.13, 0.28, 2.38, 1.07, 0.98}},
+    {128, 128, 12, 1, {0.502, 0.502, 0.502}, {2.45, 1.70, 0.98, 0.56, 0.60, 1.75}},
+    {256, 192, 1, 1, {1.061, 1.061, 1.061}, {3.75, 2.37, 3.33, 9.27, 5.25, 2.26}},
+    {256, 256, 1, 1, {1.405, 1.405, 1.405}, {4.37, 2.58, 3.90, 10.89, 7.28, 3.67}},
 };
 
 constexpr double kCUs = 256.0;
-constexpr double kFixed = 5.2;         // launch, first loads, last stores (us)
-constexpr double kHbm = 7.3e6;         // bytes per us, of which the compute units' time
-constexpr double kOverlap = 0.21;      // hides all but this share of the smaller
-constexpr double kReduce = 0.88;       // the split reduction's launch (us), ...
-constexpr double kReduceLoads = 0.32;  // each four slices it reads one after another
-constexpr double kReduceRate = 5.40e6; // and its bytes per us, partials written and read
-constexpr double kAccumulate = 2.5;    // stores that first load the old contents
-constexpr double kKmajor = 0.957;     // step time with both operands k-major
+constexpr double kFixed = 1.7;         // a launch (us)
+constexpr double kHbm = 8.1e6;         // bytes per us, of which the compute units' time
+constexpr double kOverlap = 0.17;      // hides all but this share of the smaller
+constexpr double kReduce = 2.15;       // the split reduction's launch (us), ...
+constexpr double kReduceLoads = 0.30;  // each four slices it reads one after another
+constexpr double kReduceRate = 4.45e6; // and its bytes per us, partials written and read
 
 thread_local int ov_bm = 0, ov_bn = 0, ov_splits = 1, ov_kernel = 0, ov_occ = 0;
 thread_local int ov_orients = 7;   // orientations the override applies to (bit per Orient)
@@ -145,7 +163,8 @@ const Tuned kTuned[] = {
 // Backward pairs measured fastest as one grouped launch: backward-data
 // product (m, n, k, fp32 output), backward-weight product (same) -> shared
 // tile and kernel code, splits of each product. Pairs not listed run as two
-// launches (of their tuned or modelled plans).
+// launches where both products have tuned plans, else as the model expects to be
+// faster (plan_bwd_uncached).
 struct TunedBwd {
     int64_t md, nd, kd;
     int fd;
@@ -212,26 +231,32 @@ bool fits_ws(const Gemm &g, int splits) {
 
 double out_elem(const Gemm &g) { return g.out_dtype == DT_F32 ? 4.0 : 2.0; }
 
+// Bytes read and written per element of the output.
+double out_traffic(const Gemm &g) { return out_elem(g) * (g.accumulate ? 2.0 : 1.0); }
+
 double algo_bytes(const Gemm &g) {
-    const double out = out_elem(g) * (g.accumulate ? 2.0 : 1.0);
-    return (2.0 * ((double)g.m * g.k + (double)g.k * g.n) + out * g.m * g.n) * (double)g.nbatch();
+    return (2.0 * ((double)g.m * g.k + (double)g.k * g.n) + out_traffic(g) * g.m * g.n) *
+           (double)g.nbatch();
 }
 
 double step_of(const PipeClass &c, double r) { return c.step[r > 2.0 ? 2 : r > 1.0 ? 1 : 0]; }
 
-// Work items of a product under class c: their number, one's reduction steps
-// (in units of an n-major step) and the time of its stores.
-struct Items {
-    double n, steps, epi;
-};
-Items items_of(const Gemm &g, const PipeClass &c, int splits, int per) {
+// Work items of a product under class c: their number, one's reduction steps and
+// the time of its end (see PipeClass) where `q` items of the launch come on a unit.
+double items_of(const Gemm &g, const PipeClass &c, int splits) {
     const double tiles = (double)((g.m + c.bm - 1) / c.bm) * (double)((g.n + c.bn - 1) / c.bn);
-    return {tiles * splits * (double)g.nbatch(),
-            per * (g.orient == OR_BWD_DATA ? kKmajor : 1.0),
-            c.epi * (splits > 1 ? 1.0 : g.accumulate ? kAccumulate : out_elem(g) / 4.0)};
+    return tiles * splits * (double)g.nbatch();
+}
+double end_of(const Gemm &g, const PipeClass &c, int splits, double q) {
+    const bool split = splits > 1, f32 = split || g.out_dtype == DT_F32;
+    // a row is taken to be as long as the output is wide; partials have padded rows
+    const bool cut = !split && std::fmod((double)g.n * out_elem(g), 64.0) != 0.0;
+    double t = f32 ? c.end.f32 : c.end.bf16;
+    if (cut) t += f32 ? c.end.cut_f32 : c.end.cut_bf16;
+    return c.end.least + std::min(1.0, q) * t + (g.accumulate && !split ? c.end.add : 0.0);
 }
 double reduce_time(const Gemm &g, int splits) {
-    return splits > 1 ? (4.0 * splits + out_elem(g)) * g.m * g.n / kReduceRate : 0.0;
+    return splits > 1 ? (4.0 * splits + out_traffic(g)) * g.m * g.n / kReduceRate : 0.0;
 }
 
 double reduce_loads(int splits) { return kReduceLoads * ((splits + 3) / 4); }
@@ -245,10 +270,9 @@ double overlapped(double t, double bytes) {
 // One product: the busiest unit's items in turn (beyond four the units even
 // out), not faster than its bytes, then the split reduction.
 double model_time(const Gemm &g, const PipeClass &c, int splits, int per) {
-    const Items i = items_of(g, c, splits, per);
-    const double q = i.n / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
+    const double q = items_of(g, c, splits) / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
     const double r = std::min((double)c.res, std::ceil(q));
-    const double t = busy * (i.steps * step_of(c, r) + i.epi);
+    const double t = busy * (per * step_of(c, r) + end_of(g, c, splits, q));
     return kFixed + overlapped(t, algo_bytes(g)) +
            (splits > 1 ? kReduce + reduce_loads(splits) + reduce_time(g, splits) : 0.0);
 }
@@ -256,22 +280,22 @@ double model_time(const Gemm &g, const PipeClass &c, int splits, int per) {
 // Two products sharing one grid: the longer items are dispatched first and
 // the shorter fill in behind them. The whole lasts at least as long as the
 // even share of a unit plus half a short item, and as one long item, whose
-// steps wait for the other workgroups of its unit (0.7 of taking turns with all
+// steps wait for the other workgroups of its unit (0.78 of taking turns with all
 // of them to the end: they finish sooner).
 double model_pair(const Gemm &gd, const Gemm &gw, const PipeClass &c, int sd, int pd, int sw,
                   int pw) {
-    const Items d = items_of(gd, c, sd, pd), w = items_of(gw, c, sw, pw);
-    const double q = (d.n + w.n) / kCUs, r = std::min((double)c.res, std::ceil(q));
-    const double step = step_of(c, r);
-    const double cd = d.steps * step + d.epi, cw = w.steps * step + w.epi;
+    const double nd = items_of(gd, c, sd), nw = items_of(gw, c, sw);
+    const double q = (nd + nw) / kCUs, r = std::min((double)c.res, std::ceil(q));
+    const double step = step_of(c, r), ed = end_of(gd, c, sd, q), ew = end_of(gw, c, sw, q);
+    const double cd = pd * step + ed, cw = pw * step + ew;
     const bool data_first = pd >= pw;
-    const double n1 = data_first ? d.n : w.n, c1 = data_first ? cd : cw;
+    const double n1 = data_first ? nd : nw, c1 = data_first ? cd : cw;
     const double c2 = data_first ? cw : cd;
     double t = std::max(c1, c2);
     if (q > 1.0)
-        t = std::max(std::ceil(n1 / kCUs) * c1, (d.n * cd + w.n * cw) / kCUs + 0.55 * c2);
-    const double wait = std::max(c.step[0], r > 1.0 ? 0.7 * r * step : 0.0);
-    t = std::max(t, std::max(d.steps * wait + d.epi, w.steps * wait + w.epi));
+        t = std::max(std::max(t, std::ceil(n1 / kCUs) * c1), (nd * cd + nw * cw) / kCUs + 0.58 * c2);
+    const double wait = std::max(c.step[0], r > 1.0 ? 0.78 * r * step : 0.0);
+    t = std::max(t, std::max(pd * wait + ed, pw * wait + ew));
     return kFixed + overlapped(t, algo_bytes(gd) + algo_bytes(gw)) +
            (sd > 1 || sw > 1 ? kReduce + reduce_loads(std::max(sd, sw)) : 0.0) +
            reduce_time(gd, sd) + reduce_time(gw, sw);
