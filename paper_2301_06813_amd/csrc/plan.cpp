@@ -464,16 +464,15 @@ struct PairPlan {
 thread_local std::unordered_map<PairKey, PairPlan, PairHash> pair_cache;
 }  // namespace
 
-static Plan plan_f32_uncached(const Gemm &g, bool big_ld);
-static Plan plan_f32_model(const Gemm &g, bool big_ld, double *time);
-static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, bool big_ld, Plan *pd,
+static Plan plan_f32_uncached(const Gemm &g, int mode);
+static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, int mode_d, int mode_w, Plan *pd,
                                   Plan *pw);
 
 static const Plan &cached_plan(const Gemm &g, int mode) {
     const Key k = key_of(g, mode);
     auto it = plan_cache.find(k);
     if (it != plan_cache.end()) return it->second;
-    const Plan p = g.in_dtype == DT_F32 ? plan_f32_uncached(g, mode != 0) : plan_uncached(g);
+    const Plan p = g.in_dtype == DT_F32 ? plan_f32_uncached(g, mode) : plan_uncached(g);
     if (plan_cache.size() > 4096) plan_cache.clear();
     return plan_cache.emplace(k, p).first->second;
 }
@@ -486,7 +485,20 @@ static bool f32_big_ld(const Gemm &g) {
     return g.lda > kMaxLd || g.ldb > kMaxLd;
 }
 
-Plan plan_f32(const Gemm &g) { return cached_plan(g, f32_big_ld(g)); }
+bool f32_vec4(const Gemm &g) {
+    const int64_t ca = g.orient == OR_BWD_WEIGHT ? g.m : g.k;
+    const int64_t cb = g.orient == OR_BWD_DATA ? g.k : g.n;
+    return ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) == 0 &&
+           g.lda % 4 == 0 && g.ldb % 4 == 0 && ca % 4 == 0 && cb % 4 == 0;
+}
+
+// What an fp32 plan depends on beside the sizes.
+enum { F32_BIG_LD = 1, F32_VEC4 = 2 };
+static int f32_mode(const Gemm &g) {
+    return (f32_big_ld(g) ? F32_BIG_LD : 0) | (f32_vec4(g) ? F32_VEC4 : 0);
+}
+
+Plan plan_f32(const Gemm &g) { return cached_plan(g, f32_mode(g)); }
 
 static double work_items(const Gemm &g, const Plan &p) {
     return (double)((g.m + p.bm - 1) / p.bm + 1) * (double)((g.n + p.bn - 1) / p.bn + 1) *
@@ -618,7 +630,7 @@ static bool cached_pair(const Gemm &gd, const Gemm &gw, int mode_d, int mode_w, 
     if (it == pair_cache.end()) {
         PairPlan p;
         p.grouped = gd.in_dtype == DT_F32
-                        ? plan_f32_bwd_uncached(gd, gw, mode_d || mode_w, &p.d, &p.w)
+                        ? plan_f32_bwd_uncached(gd, gw, mode_d, mode_w, &p.d, &p.w)
                         : plan_bwd_uncached(gd, gw, &p.d, &p.w);
         if (pair_cache.size() > 4096) pair_cache.clear();
         it = pair_cache.emplace(k, p).first;
@@ -633,7 +645,7 @@ bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
 }
 
 bool plan_f32_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {
-    return cached_pair(gd, gw, f32_big_ld(gd), f32_big_ld(gw), pd, pw);
+    return cached_pair(gd, gw, f32_mode(gd), f32_mode(gw), pd, pw);
 }
 
 // Generic kernel: the busiest compute unit's share of the work items, each
@@ -787,20 +799,46 @@ double f32_tiles(const Gemm &g, int t) {
     return (double)((g.m + t - 1) / t) * (double)((g.n + t - 1) / t);
 }
 constexpr double kF32Fixed = 6.0, kF32Reduce = 2.5;   // us
+// Steps below which a 128 x 128 tile's stores bound it, which more, smaller tiles
+// hide behind one another's loads (2048 x 2048 over 64 13.2 us, on 64 x 64 tiles 10.6;
+// over 160 18.7 and 16.8; 4096 x 4096 over 64 32.3 and 28.9, over 160 54.8 and 54.1).
+constexpr int kF32Steps128 = 6;
+
+// Reductions so short that the stores bound the launch, where the plain FMA
+// kernel's are faster than the matrix-core kernel's on 64 x 64 tiles: large outputs
+// (4096 x 4096 over 5 19.9 against 26.2 us, over 16 22.4 against 22.0; 960 x 1084
+// over 4 by 16-byte loads 5.8 against 5.0) and weight gradients by 4-byte loads (1123
+// x 82 over 1 4.1 against 4.6). Where the product is added to the output the
+// matrix-core kernel is faster at all sizes (2176 x 2036 over 8 10.2 against 15.6).
+bool f32_fma(const Gemm &g, int mode) {
+    if (mode & F32_BIG_LD) return true;
+    if (g.accumulate || g.k == 0) return false;
+    const double out = (double)g.m * (double)g.n;
+    if (mode & F32_VEC4) return g.k <= 8 && out >= 1 << 22;
+    return g.k <= 12 && (g.orient == OR_BWD_WEIGHT || out >= 1 << 20);
+}
 }  // namespace
 
-static Plan plan_f32_uncached(const Gemm &g, bool big_ld) {
+// The matrix-core plan the model expects to be fastest, and its time in us.
+static Plan plan_f32_model(const Gemm &g, double *time);
+
+static Plan plan_f32_uncached(const Gemm &g, int mode) {
+    if (f32_fma(g, mode)) {
+        Plan p{64, 64, 1, std::max(1, (int)((g.k + 31) / 32)), false};
+        p.bk = 32;
+        return p;
+    }
     double t;
-    return plan_f32_model(g, big_ld, &t);
+    return plan_f32_model(g, &t);
 }
 
 // The two backward products in one launch: as model_pair, with the fp32 steps.
-static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, bool big_ld, Plan *pd,
+static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, int mode_d, int mode_w, Plan *pd,
                                   Plan *pw) {
-    if (big_ld || ov_bwd_mode == 1) return false;
+    if ((mode_d | mode_w) & F32_BIG_LD || ov_bwd_mode == 1) return false;
     double best, tw;
-    *pd = plan_f32_model(gd, false, &best);
-    *pw = plan_f32_model(gw, false, &tw);
+    *pd = plan_f32_model(gd, &best);
+    *pw = plan_f32_model(gw, &tw);
     best += tw;
     bool grouped = false;
     const int kd = (int)((gd.k + 31) / 32), kw = (int)((gw.k + 31) / 32);
@@ -852,12 +890,10 @@ static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, bool big_ld, P
     return grouped;
 }
 
-static Plan plan_f32_model(const Gemm &g, bool big_ld, double *time) {
+static Plan plan_f32_model(const Gemm &g, double *time) {
     const int kb = (int)((g.k + 31) / 32);
-    Plan best{64, 64, 1, std::max(1, kb), false};
+    Plan best{64, 64, 1, std::max(1, kb), true};
     best.bk = 32;
-    if (big_ld) return best;   // plain FMA kernel
-    best.dma = true;
     *time = 1e30;
     for (const int t : {64, 128}) {
         const double nt = f32_tiles(g, t);
@@ -868,6 +904,7 @@ static Plan plan_f32_model(const Gemm &g, bool big_ld, double *time) {
             if (splits == last) continue;
             last = splits;
             if (splits > 1 && (per < 4 || !fits_ws(g, splits))) continue;
+            if (t == 128 && per < kF32Steps128) continue;
             // work items of the busiest unit; beyond four the units even out
             const double q = nt * splits / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
             const double tm = busy * per * f32_step(t, q) + kF32Fixed +

@@ -56,6 +56,38 @@ def test_f32_plans_reach_both_tiles_and_splits():
     assert all(p[3] == sbp.KERNEL_F32 for p in plans)
 
 
+def _kernel_names(fn):
+    sbp.sbp_profile_begin(8)
+    try:
+        fn()
+    finally:
+        names = [n for n, _ in sbp.sbp_profile_end(8)]
+    return names
+
+
+@pytest.mark.parametrize("M,K,N,op,acc,kernel", [
+    # stores bound these: the FMA kernel, unless they are added to the output
+    (2100, 8, 2052, "fwd", False, "gemm_f32_kernel"), (2100, 12, 2052, "fwd", False, "64"),
+    (1031, 12, 1025, "fwd", False, "gemm_f32_kernel"), (1031, 13, 1025, "fwd", False, "64"),
+    (1031, 12, 1025, "fwd", True, "64"), (12, 123, 82, "bwd_weight", False, "gemm_f32_kernel"),
+    (13, 123, 82, "bwd_weight", False, "64"), (12, 124, 84, "bwd_weight", False, "64"),
+    (12, 123, 82, "bwd_weight", True, "64"), (12, 82, 123, "fwd", False, "64"),
+    # a few steps of a 128 x 128 tile are bound by its stores
+    (2048, 160, 2048, "fwd", False, "64"), (2048, 161, 2048, "fwd", False, "128")], ids=str)
+def test_f32_short_reductions(M, K, N, op, acc, kernel):
+    X, W, dY = (_ints(a, b, 0, 0, 90 + i) for i, (a, b) in enumerate(((M, K), (K, N), (M, N))))
+    L = linear.layouts("BB", 1, 0)
+    Xd, Wd, dYd = (t.cpu().double() for t in (X, W, dY))
+    want = Xd @ Wd if op == "fwd" else Xd.t() @ dYd
+    out = torch.full(want.shape, 5.0, device="cuda")
+    names = _kernel_names(lambda: linear.run_L(op, L, X, W, dY, out, accumulate=acc))
+    assert torch.equal(out.cpu().double(), want + 5.0 if acc else want)
+    form = "gemm_f32_mfma_kernel<%s, " % kernel if kernel.isdigit() else kernel + "<"
+    assert names[0].startswith(form), names
+    if kernel.isdigit():   # the plain form holds no accumulating code
+        assert names[0].endswith(", 2>" if acc else ", 0>"), names
+
+
 def test_f32_leading_dimension_beyond_buffer_offsets():
     ld = (1 << 21) + 4
     X = torch.randint(-4, 5, (3, ld), device="cuda").float()[:, :70]
