@@ -43,12 +43,17 @@ def _check(b, h, sq, sk, d, dts, accumulate=False):
     dp = torch.full((b + 1, h, sq, sk), 9.0, dtype=dts[0], device="cuda")
     bufs["dP"] = (dp, dp[:b])
     o = {k: sbp.view4(t, scope) for k, (_, t) in bufs.items()}
-    sbp.sbp_attn_scores_bwd(v["dS"], v["Q"], v["K"], o["dQ"], o["dK"], 1, 0)
-    sbp.sbp_attn_context_bwd(v["dO"], v["P"], v["V"], o["dP"], o["dV"], 1, 0)
+    sbp.sbp_profile_begin(8)
+    try:
+        sbp.sbp_attn_scores_bwd(v["dS"], v["Q"], v["K"], o["dQ"], o["dK"], 1, 0)
+        sbp.sbp_attn_context_bwd(v["dO"], v["P"], v["V"], o["dP"], o["dV"], 1, 0)
+    finally:
+        names = [n for n, _ in sbp.sbp_profile_end(8)]
     for k, (buf, t) in bufs.items():
         w = want[k] + (9.0 if accumulate else 0.0)
         assert torch.equal(t.cpu(), w.to(t.dtype)), k
         assert bool((buf[b:] == 9.0).all()), k
+    return names
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
@@ -59,7 +64,13 @@ def test_grouped_every_instance(inst, dtype):
         try:
             sbp.sbp_set_plan_override(inst[0], inst[1], 1, inst[2])
             sbp.sbp_set_bwd_override(2, 1)
-            _check(*dims, (dtype, dtype))
+            for acc in (False, True) if dtype == torch.float32 else (False,):
+                # one launch a call: of this tile, in the accumulating form or the plain one
+                names = _check(*dims, (dtype, dtype), accumulate=acc)
+                assert len(names) == 2, names
+                for n in names:
+                    assert n.startswith("gemm_bf16_dma_bwd_kernel<%d, %d, " % inst[:2]), names
+                    assert n.endswith(", 1>") == acc, names
         finally:
             sbp.sbp_set_plan_override(0, 0, 1)
 
@@ -74,6 +85,6 @@ def test_default_plans_types_and_accumulation(dims):
     _check(*dims, (f32, f32), accumulate=True)
     try:
         sbp.sbp_set_bwd_override(1, 1)   # two launches
-        _check(*dims, (bf, bf))
+        assert len(_check(*dims, (bf, bf))) == 4
     finally:
         sbp.sbp_set_plan_override(0, 0, 1)

@@ -25,6 +25,15 @@ def _ints(rows, cols, pad, off, seed):
     return v
 
 
+def _kernel_names(fn):
+    sbp.sbp_profile_begin(8)
+    try:
+        fn()
+    finally:
+        names = [n for n, _ in sbp.sbp_profile_end(8)]
+    return names
+
+
 @pytest.mark.parametrize("pad,off", [(0, 0), (8, 4), (0, 1), (3, 0)],
                          ids=["tight", "padded", "odd-offset", "odd-ld"])
 @pytest.mark.parametrize("shape", [(1, 1, 1), (64, 128, 64), (65, 97, 130), (4, 4100, 12),
@@ -48,21 +57,59 @@ def test_f32_exact_edges(shape, pad, off):
             assert bool((guard == 5.0).all())
 
 
+@pytest.mark.parametrize("acc", [False, True], ids=["store", "add"])
+@pytest.mark.parametrize("pad,off", [(0, 0), (0, 1), (3, 0)], ids=["tight", "odd-offset", "odd-ld"])
+@pytest.mark.parametrize("m,n,k,splits", [(2052, 1540, 196, 1), (2051, 1537, 167, 1),
+                                          (1028, 1028, 1028, 3), (1025, 1027, 1030, 3)], ids=str)
+@pytest.mark.parametrize("op", range(3), ids=["fwd", "bwd_data", "bwd_weight"])
+def test_f32_128_tiles(op, m, n, k, splits, pad, off, acc):
+    # the 128 x 128 instances, cut by every edge: 16-byte and 4-byte loads, whole and
+    # split reductions, plain and accumulating
+    M, K, N = ((m, k, n), (m, n, k), (k, m, n))[op]
+    X, W, dY = (_ints(a, b, pad, off, 60 + i) for i, (a, b) in
+                enumerate(((M, K), (K, N), (M, N))))
+    Xd, Wd, dYd = (t.double() for t in (X, W, dY))
+    want = (Xd @ Wd, dYd @ Wd.t(), Xd.t() @ dYd)[op].cpu()
+    guard = torch.full((m + 2, n + 3), 5.0, device="cuda")
+    out = guard[1:-1, 1:-2]
+    say("f32 128", op, m, n, k, splits, pad, off, acc)
+    L = linear.layouts("BB", 1, 0)
+    names = _kernel_names(lambda: linear.run_L(("fwd", "bwd_data", "bwd_weight")[op], L, X, W, dY,
+                                               out, accumulate=acc))
+    assert torch.equal(out.cpu().double(), want + 5.0 if acc else want)
+    out.fill_(5.0)
+    assert bool((guard == 5.0).all())
+    assert names[0].startswith("gemm_f32_mfma_kernel<128, "), names
+    contig = {0: (k, n), 1: (k, k), 2: (m, n)}[op]
+    v = 4 if pad == off == 0 and not any(c % 4 for c in contig) else 1
+    assert names[0].endswith(", %d, %d>" % (v, 2 if acc and splits == 1 else 0)), names
+    assert (len(names) == 2) == (splits > 1), names
+
+
+@pytest.mark.parametrize("acc", [False, True], ids=["store", "add"])
+@pytest.mark.parametrize("M,K,N", [(1020, 1024, 4092), (1019, 1021, 4093)], ids=str)
+def test_f32_backward_pair_on_128_tiles(M, K, N, acc):
+    X, W, dY = (_ints(a, b, 0, 0, 70 + i) for i, (a, b) in enumerate(((M, K), (K, N), (M, N))))
+    L = linear.layouts("BB", 1, 0)
+    gx, gw = (torch.full((a + 2, b + 3), 5.0, device="cuda") for a, b in ((M, K), (K, N)))
+    dX, dW = gx[1:-1, 1:-2], gw[1:-1, 1:-2]
+    say("f32 pair 128", M, K, N, acc)
+    names = _kernel_names(lambda: linear.run_bwd_L(L, X, W, dY, dX, dW, accumulate_dw=acc))
+    want = dY.double() @ W.double().t(), X.double().t() @ dY.double()
+    assert torch.equal(dX.double(), want[0])
+    assert torch.equal(dW.double(), want[1] + 5.0 if acc else want[1])
+    dX.fill_(5.0)
+    dW.fill_(5.0)
+    assert bool((gx == 5.0).all()) and bool((gw == 5.0).all())
+    assert names[0] == "gemm_f32_mfma_bwd_kernel<128, %d, %d>" % (4 if K % 4 == 0 else 1, acc), names
+
+
 def test_f32_plans_reach_both_tiles_and_splits():
     plans = [sbp.sbp_plan(0, m, n, k, F32, F32) for m, n, k in
              ((1536, 1664, 260), (2048, 2048, 256), (4096, 4096, 512), (4, 12, 4100))]
     assert {p[0] for p in plans} == {64, 128}
     assert min(p[2] for p in plans) == 1 and max(p[2] for p in plans) > 1
     assert all(p[3] == sbp.KERNEL_F32 for p in plans)
-
-
-def _kernel_names(fn):
-    sbp.sbp_profile_begin(8)
-    try:
-        fn()
-    finally:
-        names = [n for n, _ in sbp.sbp_profile_end(8)]
-    return names
 
 
 @pytest.mark.parametrize("M,K,N,op,acc,kernel", [
@@ -130,9 +177,12 @@ def test_f32_backward_pair(shape, off):
             dX, dW = gx[1:-1, 1:-2], gw[1:-1, 1:-2]
             try:
                 sbp.sbp_set_bwd_override(mode, 1)
-                linear.run_bwd_L(L, X, W, dY, dX, dW, accumulate_dw=acc)
+                names = _kernel_names(lambda: linear.run_bwd_L(L, X, W, dY, dX, dW,
+                                                               accumulate_dw=acc))
             finally:
                 sbp.sbp_set_plan_override(0, 0, 1)
+            # the model groups all of these
+            assert names[0].startswith("gemm_f32_mfma_bwd_kernel<") == (mode == 0), names
             assert torch.equal(dX.cpu().double(), want_dx)
             assert torch.equal(dW.cpu().double(), want_dw + 5.0 if acc else want_dw)
             dX.fill_(5.0)

@@ -1,7 +1,9 @@
 """Plans chosen by the time model: valid over a range of shapes, a pure
 function of the product (kept plans do not outlive an override), and grouped
 backward plans whose partials fit the workspace."""
+import os
 import random
+import re
 
 import pytest
 
@@ -51,7 +53,19 @@ def test_backward_pair_plans_fit_and_follow_overrides(seed):
             sbp.sbp_set_plan_override(64, 64, 1, 1)
             sbp.sbp_set_bwd_override(2, 1)
             q = sbp.sbp_plan_bwd(*args)
-            assert q[1:] == (64, 64, 1, 1) or not q[0]
+            # tight rows of K and N elements: whole 16-byte blocks can be grouped
+            assert bool(q[0]) == (K % 8 == 0 and N % 8 == 0)
+            assert not q[0] or q[1:] == (64, 64, 1, 1)
         finally:
             sbp.sbp_set_plan_override(0, 0, 1)
         assert sbp.sbp_plan_bwd(*args) == p
+
+
+def test_attention_tests_cover_the_model_instances():
+    # the GPU tests' list is the planner's
+    from paper_2301_06813_amd import build
+    import test_gpu_attn_group
+    src = open(os.path.join(build.CSRC, "plan.cpp")).read()
+    rows = src.split("kPipe[] = {")[1].split("};")[0]
+    listed = {tuple(map(int, m)) for m in re.findall(r"\{(\d+), (\d+), (\d+), \d+, \{", rows)}
+    assert len(listed) == 11 and listed == set(test_gpu_attn_group.INSTANCES)
