@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <new>
 #include <unordered_map>
 
 #include "gemm.h"
@@ -468,13 +469,24 @@ static Plan plan_f32_uncached(const Gemm &g, int mode);
 static bool plan_f32_bwd_uncached(const Gemm &gd, const Gemm &gw, int mode_d, int mode_w, Plan *pd,
                                   Plan *pw);
 
-static const Plan &cached_plan(const Gemm &g, int mode) {
+// Keeps a plan for later calls; where there is no memory to keep it in, it is
+// found again next time (nothing may be thrown through the C entry points).
+template <class Cache, class K, class P>
+static void keep(Cache &cache, const K &key, const P &plan) {
+    try {
+        if (cache.size() > 4096) cache.clear();
+        cache.emplace(key, plan);
+    } catch (const std::bad_alloc &) {
+    }
+}
+
+static Plan cached_plan(const Gemm &g, int mode) {
     const Key k = key_of(g, mode);
     auto it = plan_cache.find(k);
     if (it != plan_cache.end()) return it->second;
     const Plan p = g.in_dtype == DT_F32 ? plan_f32_uncached(g, mode) : plan_uncached(g);
-    if (plan_cache.size() > 4096) plan_cache.clear();
-    return plan_cache.emplace(k, p).first->second;
+    keep(plan_cache, k, p);
+    return p;
 }
 
 Plan plan_bf16(const Gemm &g) { return cached_plan(g, dma_mode(g)); }
@@ -627,17 +639,18 @@ static bool cached_pair(const Gemm &gd, const Gemm &gw, int mode_d, int mode_w, 
     const PairKey k{key_of(gd, mode_d), key_of(gw, mode_w),
                     ov_bwd_mode * 65536 + ov_bwd_splits_w};
     auto it = pair_cache.find(k);
-    if (it == pair_cache.end()) {
-        PairPlan p;
+    PairPlan p;
+    if (it != pair_cache.end()) {
+        p = it->second;
+    } else {
         p.grouped = gd.in_dtype == DT_F32
                         ? plan_f32_bwd_uncached(gd, gw, mode_d, mode_w, &p.d, &p.w)
                         : plan_bwd_uncached(gd, gw, &p.d, &p.w);
-        if (pair_cache.size() > 4096) pair_cache.clear();
-        it = pair_cache.emplace(k, p).first;
+        keep(pair_cache, k, p);
     }
-    *pd = it->second.d;
-    *pw = it->second.w;
-    return it->second.grouped;
+    *pd = p.d;
+    *pw = p.w;
+    return p.grouped;
 }
 
 bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw) {

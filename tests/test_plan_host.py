@@ -4,6 +4,7 @@ backward plans whose partials fit the workspace."""
 import os
 import random
 import re
+import subprocess
 
 import pytest
 
@@ -69,3 +70,49 @@ def test_attention_tests_cover_the_model_instances():
     rows = src.split("kPipe[] = {")[1].split("};")[0]
     listed = {tuple(map(int, m)) for m in re.findall(r"\{(\d+), (\d+), (\d+), \d+, \{", rows)}
     assert len(listed) == 11 and listed == set(test_gpu_attn_group.INSTANCES)
+
+
+def test_planning_without_memory_does_not_throw(tmp_path):
+    # kept plans are only kept where there is memory: no exception leaves a C entry
+    src = tmp_path / "nomem.cpp"
+    src.write_text(r"""
+#include <dlfcn.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <new>
+static bool fail = false;
+void *operator new(size_t n) {
+    if (fail) throw std::bad_alloc();
+    void *p = malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+int main(int, char **argv) {
+    void *lib = dlopen(argv[1], RTLD_NOW);
+    if (!lib) return 2;
+    typedef int (*Plan)(int, int64_t, int64_t, int64_t, int32_t, int32_t, int32_t *, int32_t *,
+                        int32_t *, int32_t *);
+    typedef int (*Pair)(int64_t, int64_t, int64_t, int32_t, int64_t, int64_t, int64_t, int32_t,
+                        int32_t *, int32_t *, int32_t *, int32_t *, int32_t *);
+    Plan plan = (Plan)dlsym(lib, "sbp_plan");
+    Pair pair = (Pair)dlsym(lib, "sbp_plan_bwd");
+    int32_t a[2][4], b[2][5];
+    for (int i = 0; i < 2; ++i) {
+        fail = i == 0;
+        int rc = plan(0, 777, 555, 333, 0, 0, a[i], a[i] + 1, a[i] + 2, a[i] + 3);
+        rc |= pair(512, 640, 768, 1, 640, 768, 512, 1, b[i], b[i] + 1, b[i] + 2, b[i] + 3,
+                   b[i] + 4);
+        fail = false;
+        if (rc) return 3;
+    }
+    for (int i = 0; i < 5; ++i)
+        if (b[0][i] != b[1][i] || (i < 4 && a[0][i] != a[1][i])) return 4;
+    return 0;
+}
+""")
+    exe = str(tmp_path / "nomem")
+    subprocess.run(["g++", "-O1", "-rdynamic", "-o", exe, str(src), "-ldl"], check=True)
+    assert subprocess.run([exe, sbp.LIB_PATH]).returncode == 0
