@@ -307,6 +307,16 @@ def current_stream():
     return s
 
 
+def _forget_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+# a forked child cannot use its parent's CUDA state: it asks torch again, which
+# refuses with an error of its own
+os.register_at_fork(after_in_child=_forget_stream)
+
+
 _default_ws = {}   # (device, stream) -> (tensor, its sbp_workspace_t)
 
 

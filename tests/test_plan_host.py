@@ -116,3 +116,16 @@ int main(int, char **argv) {
     exe = str(tmp_path / "nomem")
     subprocess.run(["g++", "-O1", "-rdynamic", "-o", exe, str(src), "-ldl"], check=True)
     assert subprocess.run([exe, sbp.LIB_PATH]).returncode == 0
+
+
+def test_forked_child_forgets_the_parents_stream_lookup():
+    kept = sbp._raw_stream
+    try:
+        sbp._raw_stream = (None, None)
+        pid = os.fork()
+        if pid == 0:
+            os._exit(0 if sbp._raw_stream is None else 1)
+        assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+        assert sbp._raw_stream == (None, None)
+    finally:
+        sbp._raw_stream = kept
