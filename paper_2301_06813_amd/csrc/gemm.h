@@ -115,11 +115,11 @@ hipError_t launch_split_reduce_pair(const Gemm &gd, int sd, const float *wsd, co
 bool plan_bf16_bwd(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw);
 hipError_t launch_bf16_bwd_group(const Gemm &gd, const Plan &pd, const Gemm &gw,
                                  const Plan &pw, float *ws, hipStream_t s);
+// Whether 16-byte loads can read both operands of an fp32 product (base, leading
+// dimension and contiguous extent multiples of 4 floats).
+bool f32_vec4(const Gemm &g);
 // fp32 products: as plan_bf16 and launch_bf16 (kblk_per_split in 32-wide blocks,
 // dma false: the plain FMA kernel).
-// Whether 16-byte loads can read both operands (base, leading dimension and
-// contiguous extent multiples of 4 floats).
-bool f32_vec4(const Gemm &g);
 Plan plan_f32(const Gemm &g);
 hipError_t launch_f32(const Gemm &g, const Plan &p, float *ws, hipStream_t s);
 // fp32 forms of plan_bf16_bwd and launch_bf16_bwd_group (pd and pw are set only

@@ -294,7 +294,8 @@ double model_pair(const Gemm &gd, const Gemm &gw, const PipeClass &c, int sd, in
     const double c2 = data_first ? cw : cd;
     double t = std::max(c1, c2);
     if (q > 1.0)
-        t = std::max(std::max(t, std::ceil(n1 / kCUs) * c1), (nd * cd + nw * cw) / kCUs + 0.58 * c2);
+        t = std::max(std::max(t, std::ceil(n1 / kCUs) * c1),
+                     (nd * cd + nw * cw) / kCUs + 0.58 * c2);
     const double wait = std::max(c.step[0], r > 1.0 ? 0.78 * r * step : 0.0);
     t = std::max(t, std::max(pd * wait + ed, pw * wait + ew));
     return kFixed + overlapped(t, algo_bytes(gd) + algo_bytes(gw)) +
