@@ -41,7 +41,7 @@ const GenericTile kGeneric[] = {
 // unit), what each adds where rows are not whole 64-byte blocks, and what loading
 // the old values adds where the product is added to its output.
 //
-// Fitted on 1483 random products and 1269 random backward pairs, each on up to 45
+// Fitted on 1483 random products and 1269 random backward pairs, each on some 40
 // plans (measured from graphs of calls over three sets of operands in turn):
 // extents log-uniform in 64 .. 8192, 60 % multiples of 64 and the others of 8, up
 // to 2e11 operations; three orientations, fp32 and bf16 outputs, a third
