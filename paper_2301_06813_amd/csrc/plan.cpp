@@ -38,8 +38,9 @@ const GenericTile kGeneric[] = {
 // three or more do (`step[2]`; `res` at most), and the end of an item, `end`:
 // what it takes however few items there are, then what the stores of an fp32 or
 // a bf16 tile add when the whole chip stores (in proportion below one item per
-// unit), what each adds where rows are not whole 64-byte blocks, and what loading
-// the old values adds where the product is added to its output.
+// unit), what each adds where rows are not whole 64-byte blocks, what loading the
+// old values adds where the product is added to its output, and what an item takes
+// more in the shifted form, and there where rows are cut (0: has no such form).
 //
 // Fitted on 1483 random products and 1269 random backward pairs, each on some 40
 // plans (measured from graphs of calls over three sets of operands in turn):
@@ -52,26 +53,28 @@ const GenericTile kGeneric[] = {
 // average, 6 % (10 %) at the ninth decile, 15 % (29 %) at the 99th percentile and
 // 44 % (60 %) at worst. With the constants before, which knew neither rows cut by
 // 64-byte blocks, nor chips part filled, nor the accumulating forms, it took 6.0 %
-// (7.7 %) longer on average.
+// (7.7 %) longer on average. The last two columns were fitted on 600 products in
+// the shifted form (odd extents of 64 .. 4096); on 600 others the plan chosen takes
+// 3.1 % longer than the fastest on average, without them 8.9 %.
 struct PipeClass {
     int bm, bn, code, res;
     double step[3];
     struct {
-        double least, f32, bf16, cut_f32, cut_bf16, add;
+        double least, f32, bf16, cut_f32, cut_bf16, add, shifted, cut_shifted;
     } end;
 };
 constexpr PipeClass kPipe[] = {
-    {64, 64, 1, 2, {0.394, 0.241, 0.241}, {0.65, 0.14, 0.16, 0.22, 0.22, 0.07}},
-    {64, 64, 4, 5, {0.418, 0.312, 0.233}, {0.13, 0.29, 0.24, 0.17, 0.15, 0.18}},
-    {64, 64, 12, 1, {0.207, 0.207, 0.207}, {1.34, 0.75, 0.54, 0.32, 0.54, 0.07}},
-    {64, 128, 4, 3, {0.760, 0.356, 0.339}, {0.79, 0.30, 0.24, 1.01, 0.58, 0.05}},
-    {64, 128, 12, 1, {0.409, 0.409, 0.409}, {1.78, 1.26, 0.51, 0.25, 0.64, 0.36}},
-    {128, 64, 4, 3, {0.755, 0.334, 0.309}, {0.60, 0.33, 0.21, 0.73, 0.22, 0.19}},
-    {128, 64, 12, 1, {0.367, 0.367, 0.367}, {1.87, 1.24, 0.59, 0.29, 0.70, 0.30}},
-    {128, 128, 4, 2, {0.792, 0.388, 0.388}, {2.07, 0.13, 0.28, 2.38, 1.07, 0.98}},
-    {128, 128, 12, 1, {0.502, 0.502, 0.502}, {2.45, 1.70, 0.98, 0.56, 0.60, 1.75}},
-    {256, 192, 1, 1, {1.061, 1.061, 1.061}, {3.75, 2.37, 3.33, 9.27, 5.25, 2.26}},
-    {256, 256, 1, 1, {1.405, 1.405, 1.405}, {4.37, 2.58, 3.90, 10.89, 7.28, 3.67}},
+    {64, 64, 1, 2, {0.394, 0.241, 0.241}, {0.65, 0.14, 0.16, 0.22, 0.22, 0.07, 1.0, -0.3}},
+    {64, 64, 4, 5, {0.418, 0.312, 0.233}, {0.13, 0.29, 0.24, 0.17, 0.15, 0.18, 0.0, 0.0}},
+    {64, 64, 12, 1, {0.207, 0.207, 0.207}, {1.34, 0.75, 0.54, 0.32, 0.54, 0.07, 1.9, 1.8}},
+    {64, 128, 4, 3, {0.760, 0.356, 0.339}, {0.79, 0.30, 0.24, 1.01, 0.58, 0.05, 0.0, 0.0}},
+    {64, 128, 12, 1, {0.409, 0.409, 0.409}, {1.78, 1.26, 0.51, 0.25, 0.64, 0.36, 1.4, 2.8}},
+    {128, 64, 4, 3, {0.755, 0.334, 0.309}, {0.60, 0.33, 0.21, 0.73, 0.22, 0.19, 0.0, 0.0}},
+    {128, 64, 12, 1, {0.367, 0.367, 0.367}, {1.87, 1.24, 0.59, 0.29, 0.70, 0.30, 2.0, 3.6}},
+    {128, 128, 4, 2, {0.792, 0.388, 0.388}, {2.07, 0.13, 0.28, 2.38, 1.07, 0.98, 1.0, 0.4}},
+    {128, 128, 12, 1, {0.502, 0.502, 0.502}, {2.45, 1.70, 0.98, 0.56, 0.60, 1.75, 2.7, 7.7}},
+    {256, 192, 1, 1, {1.061, 1.061, 1.061}, {3.75, 2.37, 3.33, 9.27, 5.25, 2.26, 0.0, 0.0}},
+    {256, 256, 1, 1, {1.405, 1.405, 1.405}, {4.37, 2.58, 3.90, 10.89, 7.28, 3.67, 0.0, 0.0}},
 };
 
 constexpr double kCUs = 256.0;
@@ -99,8 +102,9 @@ using sbpk::EPI_STAGED;
 constexpr Instance kInstances[] = {
     {1, 256, 256, 0, 1, EPI_DIRECT}, {1, 256, 192, 0, 1, EPI_DIRECT},
     {1, 256, 128, 0, 1, EPI_DIRECT}, {1, 128, 256, 0, 1, EPI_DIRECT},
-    {1, 128, 128, 0, 1, EPI_DIRECT}, {1, 128, 64, 0, 1, EPI_DIRECT},  {1, 64, 128, 0, 1, EPI_DIRECT},
-    {1, 64, 64, 0, 1, EPI_DIRECT},   {4, 128, 128, 2, 1, EPI_DIRECT}, {5, 256, 128, 0, 2, EPI_STAGED},
+    {1, 128, 128, 0, 1, EPI_DIRECT}, {1, 128, 64, 0, 1, EPI_DIRECT},
+    {1, 64, 128, 0, 1, EPI_DIRECT},  {1, 64, 64, 0, 1, EPI_DIRECT},
+    {4, 128, 128, 2, 1, EPI_DIRECT}, {5, 256, 128, 0, 2, EPI_STAGED},
     {5, 128, 256, 0, 2, EPI_STAGED}, {5, 128, 128, 0, 2, EPI_STAGED}, {6, 256, 256, 0, 1, EPI_ROWQ},
     {6, 128, 128, 2, 1, EPI_ROWQ},   {7, 256, 128, 0, 2, EPI_ROWQ},   {7, 128, 256, 0, 2, EPI_ROWQ},
     {7, 128, 128, 0, 2, EPI_ROWQ},   {8, 256, 256, 5, 1, EPI_DIRECT, 32},
@@ -248,13 +252,14 @@ double items_of(const Gemm &g, const PipeClass &c, int splits) {
     const double tiles = (double)((g.m + c.bm - 1) / c.bm) * (double)((g.n + c.bn - 1) / c.bn);
     return tiles * splits * (double)g.nbatch();
 }
-double end_of(const Gemm &g, const PipeClass &c, int splits, double q) {
+double end_of(const Gemm &g, const PipeClass &c, int splits, double q, bool shift) {
     const bool split = splits > 1, f32 = split || g.out_dtype == DT_F32;
     // a row is taken to be as long as the output is wide; partials have padded rows
     const bool cut = !split && std::fmod((double)g.n * out_elem(g), 64.0) != 0.0;
     double t = f32 ? c.end.f32 : c.end.bf16;
-    if (cut) t += f32 ? c.end.cut_f32 : c.end.cut_bf16;
-    return c.end.least + std::min(1.0, q) * t + (g.accumulate && !split ? c.end.add : 0.0);
+    if (cut) t += (f32 ? c.end.cut_f32 : c.end.cut_bf16) + (shift ? c.end.cut_shifted : 0.0);
+    return c.end.least + std::min(1.0, q) * t + (g.accumulate && !split ? c.end.add : 0.0) +
+           (shift ? c.end.shifted : 0.0);
 }
 double reduce_time(const Gemm &g, int splits) {
     return splits > 1 ? (4.0 * splits + out_traffic(g)) * g.m * g.n / kReduceRate : 0.0;
@@ -270,10 +275,10 @@ double overlapped(double t, double bytes) {
 
 // One product: the busiest unit's items in turn (beyond four the units even
 // out), not faster than its bytes, then the split reduction.
-double model_time(const Gemm &g, const PipeClass &c, int splits, int per) {
+double model_time(const Gemm &g, const PipeClass &c, int splits, int per, bool shift) {
     const double q = items_of(g, c, splits) / kCUs, busy = q > 4.0 ? q + 0.5 : std::ceil(q);
     const double r = std::min((double)c.res, std::ceil(q));
-    const double t = busy * (per * step_of(c, r) + end_of(g, c, splits, q));
+    const double t = busy * (per * step_of(c, r) + end_of(g, c, splits, q, shift));
     return kFixed + overlapped(t, algo_bytes(g)) +
            (splits > 1 ? kReduce + reduce_loads(splits) + reduce_time(g, splits) : 0.0);
 }
@@ -284,10 +289,11 @@ double model_time(const Gemm &g, const PipeClass &c, int splits, int per) {
 // steps wait for the other workgroups of its unit (0.78 of taking turns with all
 // of them to the end: they finish sooner).
 double model_pair(const Gemm &gd, const Gemm &gw, const PipeClass &c, int sd, int pd, int sw,
-                  int pw) {
+                  int pw, bool shift) {
     const double nd = items_of(gd, c, sd), nw = items_of(gw, c, sw);
     const double q = (nd + nw) / kCUs, r = std::min((double)c.res, std::ceil(q));
-    const double step = step_of(c, r), ed = end_of(gd, c, sd, q), ew = end_of(gw, c, sw, q);
+    const double step = step_of(c, r);
+    const double ed = end_of(gd, c, sd, q, shift), ew = end_of(gw, c, sw, q, shift);
     const double cd = pd * step + ed, cw = pw * step + ew;
     const bool data_first = pd >= pw;
     const double n1 = data_first ? nd : nw, c1 = data_first ? cd : cw;
@@ -619,7 +625,7 @@ static bool plan_bwd_uncached(const Gemm &gd, const Gemm &gw, Plan *pd, Plan *pw
                 if (sw == last_w) continue;
                 last_w = sw;
                 if (sw > 1 && perw < 2) continue;
-                const double tm = model_pair(gd, gw, c, sd, perd, sw, perw);
+                const double tm = model_pair(gd, gw, c, sd, perd, sw, perw, sh);
                 if (tm >= best * 0.999) continue;
                 Plan qd, qw;
                 if (!grouped_plan(gd, gw, &in, c.bm, c.bn, sd, sw, &qd, &qw)) continue;
@@ -784,7 +790,7 @@ static Plan plan_model(const Gemm &g, double *time) {
             last_splits = splits;
             if (splits > 1 && per < 2) continue;            // keep >= 128 reduction per split
             if (!fits_ws(g, splits)) continue;
-            const double tm = model_time(g, c, splits, per);
+            const double tm = model_time(g, c, splits, per, shift);
             if (tm < *time * 0.999) {
                 *time = tm;
                 best = Plan{c.bm, c.bn, splits, per, true, in.ns, in.kg, in.epi, 0, in.bk};

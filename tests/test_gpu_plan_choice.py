@@ -1,6 +1,6 @@
 """The plan that the time model chooses is near the fastest of the plans it chooses
 among, for products whose choice was once wrong: accumulating outputs, outputs of a
-few tiles, rows that are not whole 64-byte blocks."""
+few tiles, rows that are not whole 64-byte blocks, operands in the shifted form."""
 import pytest
 import torch
 
@@ -17,10 +17,14 @@ pytestmark = pytest.mark.gpu
     ("bwd_weight", "DP", (896, 4160, 192), True), ("bwd_weight", "DP", (256, 2048, 576), True),
     ("bwd_weight", "DP", (64, 3712, 512), True), ("bwd_weight", "DP", (2048, 6016, 512), True),
     ("bwd_weight", "DP", (384, 192, 384), False), ("bwd_weight", "DP", (560, 1456, 424), False),
-    ("fwd", "DP", (2592, 64, 4120), False), ("bwd_data", "COL", (6080, 192, 64), False)], ids=str)
+    ("fwd", "DP", (2592, 64, 4120), False), ("bwd_data", "COL", (6080, 192, 64), False),
+    ("bwd_weight", "DP", (248, 2803, 1171), False), ("fwd", "DP", (785, 523, 2037), False),
+    ("bwd_data", "COL", (1643, 1951, 238), False)], ids=str)
 def test_chosen_plan_is_near_the_fastest(op, sig, shape, acc):
     M, K, N = shape
-    X, W, dY = (torch.randn(a, b, device="cuda").bfloat16() for a, b in ((M, K), (K, N), (M, N)))
+    # rows that start on 16-byte blocks
+    X, W, dY = (torch.randn(a, -(-b // 8) * 8, device="cuda").bfloat16()[:, :b]
+                for a, b in ((M, K), (K, N), (M, N)))
     L = linear.layouts(sig, 1, 0)
     out = linear.alloc_out_L(op, L, M, K, N, torch.bfloat16, "cuda")
     out = (out.float() if acc else out).zero_()
